@@ -62,6 +62,10 @@ struct mhd_box {
     char* tw[3];       // per-axis FFT twiddles (n complex values)
     double* sf[3];     // per-axis 27-point stencil factors (n values)
     int cur[3];        // current slot of the groups H, M, B
+    // cells per segment of the marching kernels (march_segments): the NONADV
+    // faces along y and z, the ADV faces along y, the fused ADV update and the
+    // face-field update along z
+    int seg_fy, seg_fz, seg_ay, seg_xz, seg_b;
     // per-launch event timing (mhd_set_timing)
     int timing;
     int nev;
@@ -133,6 +137,7 @@ size_t face_values(bool ion) { return ion ? NFACE + 1 : NFACE; }
 
 ZTile ztile_of(const Geo& g, int nt, int txmax = 64);
 int ztile_blocks(const Geo& g, const ZTile& z);
+void march_segments(mhd_box* b, double share);
 
 Layout layout_of(const int32_t n[3], int precision, bool grav, bool ion)
 {
@@ -210,6 +215,7 @@ void box_bind(mhd_box* b, const mhd_params* p, const Layout& L)
         }
     }
     b->cur[0] = b->cur[1] = b->cur[2] = 0;
+    march_segments(b, 1.0);
     b->timing = 0;
     b->nev = 0;
     b->ev_ready = 0;
@@ -421,8 +427,37 @@ struct MultiEmit {
 
 // ---------------------------------------------------------------- the step program
 
-// z cells per thread in the z-marching update kernels
+// longest segment of a marching kernel (longer ones leave the last blocks of
+// a large box too uneven: 64 cells cost 1-2% at 256^3)
 constexpr int ZMARCH_SEG = 32;
+
+// Segment length of a march over nd cells.  `units` units of work (waves or
+// blocks) per segment run on `slots` places (SIMDs or CUs), `occ` at a time on
+// each; a further resident unit costs `more` of the time of one alone; starting
+// a segment costs `fixed` cells.  A box of few cells wants short segments: a
+// march is a serial chain (2 us per face, 3 us per plane of the fused ADV
+// update), and 32^3 cells in segments of 32 keep 16 waves busy on 1024 SIMDs
+// (1365 us a step; with short ones every launch takes the time of a few
+// cells).  A large box wants long ones, whose start is a small part.  The
+// parameters are fitted to steps of 32^3 to 256^3 cells at segments of 1 to
+// 64; the segments are of even length, so that no launch ends on a short one.
+// Only the order of the work depends on the choice, not its results.
+int best_segment(int nd, double units, int slots, int occ, double more, double fixed)
+{
+    int best = 1;
+    double cost = 1e300;
+    for (int len = nd < ZMARCH_SEG ? nd : ZMARCH_SEG; len >= 1; len--) {
+        const int nseg = (nd + len - 1) / len, seg = (nd + nseg - 1) / nseg;
+        const double m = std::ceil(units * nseg / slots);
+        const double full = std::floor(m / occ), rem = m - full * occ;
+        const double c = (full * (1.0 + more * (occ - 1)) + (rem > 0.0 ? 1.0 + more * (rem - 1.0) : 0.0)) * (seg + fixed);
+        if (c < cost) {
+            cost = c;
+            best = seg;
+        }
+    }
+    return best;
+}
 
 // tiles of the z-marching update kernels: 64 x cells (a wave) by nt / 64
 // rows for blocks of nt threads, narrower for thin boxes
@@ -455,19 +490,38 @@ int xz_block_threads(const Geo& g, size_t esz)
 
 bool adv_xz(const Geo& g, size_t esz) { return xz_block_threads(g, esz) > 0; }
 
-// rows per block, row groups and z segment of the fused ADV update
-void xz_tiling(const Geo& g, size_t esz, int& rpb, int& nrg, int& seg)
+// rows per block and row groups of the fused ADV update
+void xz_tiling(const Geo& g, size_t esz, int& rpb, int& nrg)
 {
     rpb = xz_block_threads(g, esz) / g.nx;
     nrg = (g.ny + rpb - 1) / rpb;
-    seg = g.nz < ZMARCH_SEG ? g.nz : ZMARCH_SEG;
 }
 
-int xz_blocks(const Geo& g, size_t esz)
+// segments of the box's marching kernels; the box's share of the launches it
+// takes part in is 1 / share (a server's launches cover all boxes in flight)
+void march_segments(mhd_box* b, double share)
 {
-    int rpb, nrg, seg;
-    xz_tiling(g, esz, rpb, nrg, seg);
-    return nrg * ((g.nz + seg - 1) / seg);
+    constexpr int CU = 256, SIMD = 4 * CU;   // MI355X
+    const Geo& g = b->g;
+    const bool d = b->esz == 8;
+    auto waves = [&](double threads) { return share * threads / 64.0; };
+    // NONADV faces: two (FP64) or three waves per SIMD
+    const int occ = d ? 2 : 3;
+    const double more = d ? 0.65 : 0.4;
+    b->seg_fy = best_segment(g.ny, waves((double)g.nx * g.nz), SIMD, occ, more, d ? 1.5 : 2.5);
+    b->seg_fz = best_segment(g.nz, waves((double)g.nx * g.ny), SIMD, occ, more, d ? 1.5 : 2.5);
+    b->seg_ay = best_segment(g.ny, waves((double)g.nx * g.nz), SIMD, d ? 2 : 4, d ? 0.65 : 0.35, 2.5);
+    const int nt = xz_block_threads(g, b->esz);
+    b->seg_xz = ZMARCH_SEG;
+    if (nt > 0) {
+        int rpb, nrg;
+        xz_tiling(g, b->esz, rpb, nrg);
+        // blocks per CU: three (FP64) or four of 256 threads, two of 512 in
+        // FP32, one of the larger ones
+        const int per_cu = nt == 256 ? (d ? 3 : 4) : (nt == 512 && !d ? 2 : 1);
+        b->seg_xz = best_segment(g.nz, share * nrg, CU, per_cu, d ? 0.6 : 0.5, 1.0);
+    }
+    b->seg_b = best_segment(g.nz, waves((double)g.nx * g.ny), SIMD, 4, 0.25, 0.7);
 }
 
 // One NONADV substage.  y and z faces first (marching kernels); then, for
@@ -501,11 +555,10 @@ void emit_nonadv_substage_t(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout
     fa.dbg = dbg;
     fa.phi = phi;
     // y and z faces: marching segments
-    constexpr int MARCH_SEG = 32;
     for (int D = 1; D <= 2; D++) {
         const int nd = D == 1 ? g.ny : g.nz;
         const int no = D == 1 ? g.nz : g.ny;
-        fa.seg = nd < MARCH_SEG ? nd : MARCH_SEG;
+        fa.seg = D == 1 ? b->seg_fy : b->seg_fz;
         fa.rpb = 0;
         fa.F = D == 1 ? F1 : F2;
         long long threads = (long long)g.nx * no * ((nd + fa.seg - 1) / fa.seg);
@@ -548,6 +601,7 @@ void emit_nonadv_substage_t(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout
     ua.rk = rk;
     ua.dbg = dbg;
     ua.zt = ztile_of(g, UPD_NT, UPD_TX);
+    ua.zt.seg = b->seg_b;
     ua.phi = phi;
     const int ublocks = ztile_blocks(g, ua.zt);
     if (rows)
@@ -576,8 +630,7 @@ void emit_adv_face(mhd_box* b, Emit& e, const Fields<T>& in, const StepArgs& a)
         ma.U = cview(in);
         ma.a = a;
         ma.F = reinterpret_cast<T*>(b->F[1]);
-        constexpr int SEG = 32;
-        ma.seg = b->g.ny < SEG ? b->g.ny : SEG;
+        ma.seg = b->seg_ay;
         long long threads = (long long)b->g.nx * b->g.nz * ((b->g.ny + ma.seg - 1) / ma.seg);
         e.template launch<BAdvFaceMarchY<T, NQ>>(MHD_K_ADV_FACE, (int)((threads + NTH - 1) / NTH), 0, ma);
     } else {
@@ -633,11 +686,13 @@ void emit_adv_substage(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout, con
         xa.a = a;
         xa.rk = rk;
         xa.dbg = dbg;
-        xz_tiling(b->g, sizeof(T), xa.rpb, xa.nrg, xa.seg);
+        xz_tiling(b->g, sizeof(T), xa.rpb, xa.nrg);
+        xa.seg = b->seg_xz;
         const int nt = xz_block_threads(b->g, sizeof(T));
-        if (nt == 256) emit_adv_xz<T, 256>(e, xa, xz_blocks(b->g, sizeof(T)), ion);
-        else if (nt == 512) emit_adv_xz<T, 512>(e, xa, xz_blocks(b->g, sizeof(T)), ion);
-        else if constexpr (sizeof(T) == 4) emit_adv_xz<T, 1024>(e, xa, xz_blocks(b->g, sizeof(T)), ion);
+        const int blocks = xa.nrg * ((b->g.nz + xa.seg - 1) / xa.seg);
+        if (nt == 256) emit_adv_xz<T, 256>(e, xa, blocks, ion);
+        else if (nt == 512) emit_adv_xz<T, 512>(e, xa, blocks, ion);
+        else if constexpr (sizeof(T) == 4) emit_adv_xz<T, 1024>(e, xa, blocks, ion);
         return;
     }
     // x faces from staged row segments, one face per thread; y faces marched
@@ -1147,10 +1202,13 @@ int server_step(mhd_server* sv, int half)
 {
     sv->recs.clear();
     MultiEmit e{ &sv->recs, 0, true, false };
+    double cells = 0.0;
+    for (const mhd_server::Active& a : sv->active) cells += (double)a.box->g.n;
     for (size_t i = 0; i < sv->active.size(); i++) {
         mhd_box* b = sv->active[i].box;
         e.k = 0;
         e.first = i == 0;
+        march_segments(b, cells / (double)b->g.n);
         StepArgs a = step_args(b, 0.0, true);
         emit_step<T>(b, e, a);
         if (e.mismatch || e.k != sv->recs.size()) return MHD_EINVAL;
