@@ -135,8 +135,6 @@ bool valid_params(const mhd_params* p)
 // ionisation network
 size_t face_values(bool ion) { return ion ? NFACE + 1 : NFACE; }
 
-ZTile ztile_of(const Geo& g, int nt, int txmax = 64);
-int ztile_blocks(const Geo& g, const ZTile& z);
 void march_segments(mhd_box* b, double share);
 
 Layout layout_of(const int32_t n[3], int precision, bool grav, bool ion)
@@ -150,16 +148,9 @@ Layout layout_of(const int32_t n[3], int precision, bool grav, bool ion)
     // the face scratch doubles as host staging (MHD_NPRIM or NF FP64 fields)
     size_t stage = align256((size_t)NF * N * 8);
     L.F = 3 * fbytes > stage ? 3 * fbytes : stage;
-    // per-block partials: the totals (NF per cell-parallel block) and the
-    // CFL speed maxima of the z-marching update that runs the tail
-    Geo g;
-    g.nx = n[0];
-    g.ny = n[1];
-    g.nz = n[2];
-    g.nxy = n[0] * n[1];
-    g.n = (int)N;
-    size_t zb = (size_t)ztile_blocks(g, ztile_of(g, NTH));
-    L.part = align256((nb * NF > zb ? nb * NF : zb) * sizeof(double));
+    // per-block partials: the totals (NF per cell-parallel block); the CFL
+    // speed maxima need one
+    L.part = align256(nb * NF * sizeof(double));
     L.misc = 3 * 256;
     // self-gravity: the potential and the FFT tables (the complex scratch of
     // the Poisson solve is the x face scratch, free at that point)
@@ -175,11 +166,7 @@ Layout layout_of(const int32_t n[3], int precision, bool grav, bool ion)
 void box_bind(mhd_box* b, const mhd_params* p, const Layout& L)
 {
     b->p = *p;
-    b->g.nx = p->n[0];
-    b->g.ny = p->n[1];
-    b->g.nz = p->n[2];
-    b->g.nxy = p->n[0] * p->n[1];
-    b->g.n = p->n[0] * p->n[1] * p->n[2];
+    b->g = make_geo(p->n[0], p->n[1], p->n[2]);
     b->s = reinterpret_cast<hipStream_t>(p->stream);
     b->prec = p->precision;
     b->esz = p->precision == MHD_FP64 ? 8 : 4;
@@ -459,8 +446,8 @@ int best_segment(int nd, double units, int slots, int occ, double more, double f
     return best;
 }
 
-// tiles of the z-marching update kernels: 64 x cells (a wave) by nt / 64
-// rows for blocks of nt threads, narrower for thin boxes
+// tiles of the face-field update: 64 x cells (a wave) by nt / 64 rows for
+// blocks of nt threads, narrower for thin boxes
 ZTile ztile_of(const Geo& g, int nt, int txmax)
 {
     ZTile z;
@@ -477,24 +464,47 @@ int ztile_blocks(const Geo& g, const ZTile& z)
     return z.ntx * z.nty * ((g.nz + z.seg - 1) / z.seg);
 }
 
-// The ADV update forms the x faces itself when whole x rows fit its block:
-// blocks of 256 threads, or 512 for longer rows, or 1024 for FP32 state (the
-// FP64 kernels need more than the 128 registers a 1024-thread block allows).
-int xz_block_threads(const Geo& g, size_t esz)
+// Row segments for blocks of nt threads: the split whose blocks hold the most
+// own cells, on a tie the fewer pieces.  A block that is not full costs as much
+// as a full one even where whole waves have no cells (they hold registers and
+// LDS: FP64 rows of 512 cells as 3 pieces of 171 in three of four waves take
+// 96 ps per cell and launch pair of the fused ADV update, as 9 pieces with four
+// in a block 82 ps).
+RowTile row_tile(int nx, int nt)
 {
-    if (g.nx <= 256) return 256;
-    if (g.nx <= 512) return 512;
-    if (g.nx <= 1024 && esz == 4) return 1024;
-    return 0;
+    RowTile best{};
+    double most = -1.0;
+    for (int spr = 1; spr <= nx && spr <= 16 + nx / (nt - 6); spr++) {
+        RowTile t{};
+        t.spr = spr;
+        t.tx = (nx + spr - 1) / spr;
+        t.w = spr == 1 ? nx : t.tx + 6;
+        if (t.w > nt || (long long)t.tx * (spr - 1) >= nx) continue;   // too wide, or an empty last piece
+        t.rpb = nt / t.w;
+        const double own = (double)nx / spr * t.rpb;
+        if (own > most + 1e-9) {
+            most = own;
+            best = t;
+        }
+    }
+    best.dspr = fast_div(best.spr);
+    best.dw = fast_div(best.w);
+    return best;
 }
 
-bool adv_xz(const Geo& g, size_t esz) { return xz_block_threads(g, esz) > 0; }
+// Row segments of the kernels with x rows, in blocks of 256 threads.  FP32
+// takes whole rows of up to 512 cells in blocks of 512 where these lose no
+// more lanes than the pieces (rows of 512: x-row kernel 791 against 857 us at
+// 128 x 512 x 512, fused ADV update 44 against 47 ps per cell and launch pair;
+// rows of 367: level).  In FP64 the pieces are faster (rows of 512: 67 against
+// 74 and 82 against 90 ps): blocks of 512 leave a CU at two waves per SIMD.
+constexpr int ROW_NT = 256;
 
-// rows per block and row groups of the fused ADV update
-void xz_tiling(const Geo& g, size_t esz, int& rpb, int& nrg)
+bool wide_rows(const Geo& g, size_t esz)
 {
-    rpb = xz_block_threads(g, esz) / g.nx;
-    nrg = (g.ny + rpb - 1) / rpb;
+    if (esz == 8 || g.nx <= ROW_NT || g.nx > 512) return false;
+    const RowTile t = row_tile(g.nx, ROW_NT);
+    return g.nx / 512.0 >= 0.95 * ((double)g.nx / t.spr * t.rpb / ROW_NT);
 }
 
 // segments of the box's marching kernels; the box's share of the launches it
@@ -511,24 +521,18 @@ void march_segments(mhd_box* b, double share)
     b->seg_fy = best_segment(g.ny, waves((double)g.nx * g.nz), SIMD, occ, more, d ? 1.5 : 2.5);
     b->seg_fz = best_segment(g.nz, waves((double)g.nx * g.ny), SIMD, occ, more, d ? 1.5 : 2.5);
     b->seg_ay = best_segment(g.ny, waves((double)g.nx * g.nz), SIMD, d ? 2 : 4, d ? 0.65 : 0.35, 2.5);
-    const int nt = xz_block_threads(g, b->esz);
-    b->seg_xz = ZMARCH_SEG;
-    if (nt > 0) {
-        int rpb, nrg;
-        xz_tiling(g, b->esz, rpb, nrg);
-        // blocks per CU: three (FP64) or four of 256 threads, two of 512 in
-        // FP32, one of the larger ones
-        const int per_cu = nt == 256 ? (d ? 3 : 4) : (nt == 512 && !d ? 2 : 1);
-        b->seg_xz = best_segment(g.nz, share * nrg, CU, per_cu, d ? 0.6 : 0.5, 1.0);
-    }
+    // fused ADV update: three (FP64) or four blocks of 256 threads per CU, two
+    // of 512
+    const bool wide = wide_rows(g, b->esz);
+    const RowTile rt = row_tile(g.nx, wide ? 512 : ROW_NT);
+    const double groups = std::ceil((double)g.ny * rt.spr / rt.rpb);
+    b->seg_xz = best_segment(g.nz, share * groups, CU, wide ? 2 : (d ? 3 : 4), d ? 0.6 : 0.5, 1.0);
     b->seg_b = best_segment(g.nz, waves((double)g.nx * g.ny), SIMD, 4, 0.25, 0.7);
 }
 
-// One NONADV substage.  y and z faces first (marching kernels); then, for
-// boxes whose x rows fit a block, the x-row face kernel, which also updates
-// m, E and e, and the face-field update; otherwise the one-face-per-thread x
-// kernel and the full update.  The primitives are formed inside the face
-// kernels from the substage input state.
+// One NONADV substage: y and z faces (marching kernels), the x-row face kernel,
+// which also updates m, E and e, and the face-field update.  The primitives are
+// formed inside the face kernels from the substage input state.
 template <typename T, bool ION, class Emit>
 void emit_nonadv_substage_t(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout, const StepArgs& a, RK rk,
                             int dbg, bool first)
@@ -559,7 +563,6 @@ void emit_nonadv_substage_t(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout
         const int nd = D == 1 ? g.ny : g.nz;
         const int no = D == 1 ? g.nz : g.ny;
         fa.seg = D == 1 ? b->seg_fy : b->seg_fz;
-        fa.rpb = 0;
         fa.F = D == 1 ? F1 : F2;
         long long threads = (long long)g.nx * no * ((nd + fa.seg - 1) / fa.seg);
         int blocks = (int)((threads + NTH - 1) / NTH);
@@ -573,23 +576,16 @@ void emit_nonadv_substage_t(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout
     fa.F = F0;
     fa.seg = 0;
     fa.dt_cfl = first ? b->dt_dev : nullptr;
-    const int maxt = sizeof(T) == 8 ? 512 : 1024;
-    const bool rows = g.nx <= maxt;
-    if (rows) {
-        int rpb = g.nx >= 256 ? 1 : 256 / g.nx;
-        fa.rpb = rpb;
-        int blocks = (g.ny * g.nz + rpb - 1) / rpb;
-        if (g.nx <= 256)
-            e.template launch<BFaceXRows<T, 256, ION>>(MHD_K_NONADV_FACE, blocks, 256 * XROW_SLOTS * sizeof(T), fa);
-        else if (g.nx <= 512)
-            e.template launch<BFaceXRows<T, 512, ION>>(MHD_K_NONADV_FACE, blocks, 512 * XROW_SLOTS * sizeof(T), fa);
-        else if constexpr (sizeof(T) == 4)   // 1024-thread rows only in FP32 (register budget)
-            e.template launch<BFaceXRows<T, 1024, ION>>(MHD_K_NONADV_FACE, blocks, 1024 * XROW_SLOTS * sizeof(T), fa);
-    } else {
-        fa.rpb = 0;
-        e.template launch<BFacePair<T, 0, ION>>(MHD_K_NONADV_FACE, b->nblocks, 0, fa);
+    const bool wide = wide_rows(g, sizeof(T));
+    fa.rt = row_tile(g.nx, wide ? 512 : ROW_NT);
+    const int xblocks = (int)(((long long)g.ny * g.nz * fa.rt.spr + fa.rt.rpb - 1) / fa.rt.rpb);
+    if constexpr (sizeof(T) == 4) {
+        if (wide)
+            e.template launch<BFaceXRows<T, 512, ION>>(MHD_K_NONADV_FACE, xblocks, 512 * XROW_SLOTS * sizeof(T), fa);
     }
-    NonadvUpdateArgs<T> ua;
+    if (!wide)
+        e.template launch<BFaceXRows<T, ROW_NT, ION>>(MHD_K_NONADV_FACE, xblocks, ROW_NT * XROW_SLOTS * sizeof(T), fa);
+    FieldUpdateArgs<T> ua;
     ua.g = g;
     ua.U = cview(in);
     ua.S = cview(S);
@@ -602,12 +598,7 @@ void emit_nonadv_substage_t(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout
     ua.dbg = dbg;
     ua.zt = ztile_of(g, UPD_NT, UPD_TX);
     ua.zt.seg = b->seg_b;
-    ua.phi = phi;
-    const int ublocks = ztile_blocks(g, ua.zt);
-    if (rows)
-        e.template launch<BNonadvUpdate<T, ION, false>>(MHD_K_NONADV_UPDATE, ublocks, 0, ua);
-    else
-        e.template launch<BNonadvUpdate<T, ION, true>>(MHD_K_NONADV_UPDATE, ublocks, 0, ua);
+    e.template launch<BFieldUpdate<T>>(MHD_K_NONADV_UPDATE, ztile_blocks(g, ua.zt), 0, ua);
 }
 
 template <typename T, class Emit>
@@ -620,37 +611,19 @@ void emit_nonadv_substage(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout, 
         emit_nonadv_substage_t<T, false>(b, e, sin, sS, sout, a, rk, dbg, first);
 }
 
-template <typename T, int D, int NQ, class Emit>
+// ADV faces along y, marched along y
+template <typename T, int NQ, class Emit>
 void emit_adv_face(mhd_box* b, Emit& e, const Fields<T>& in, const StepArgs& a)
 {
-    if constexpr (D == 1) {
-        // y faces: marched along y
-        typename BAdvFaceMarchY<T, NQ>::Args ma;
-        ma.g = b->g;
-        ma.U = cview(in);
-        ma.a = a;
-        ma.F = reinterpret_cast<T*>(b->F[1]);
-        ma.seg = b->seg_ay;
-        long long threads = (long long)b->g.nx * b->g.nz * ((b->g.ny + ma.seg - 1) / ma.seg);
-        e.template launch<BAdvFaceMarchY<T, NQ>>(MHD_K_ADV_FACE, (int)((threads + NTH - 1) / NTH), 0, ma);
-    } else {
-        // x faces from row segments staged in LDS
-        static_assert(D == 0, "y faces are marched");
-        typename BAdvFaceXRow<T, NQ>::Args fa;
-        const Geo& g = b->g;
-        fa.g = g;
-        fa.U = cview(in);
-        fa.a = a;
-        fa.F = reinterpret_cast<T*>(b->F[0]);
-        fa.tx = g.nx < NTH ? g.nx : NTH;
-        fa.spr = (g.nx + fa.tx - 1) / fa.tx;
-        fa.rpb = NTH / fa.tx < NTH / 6 ? NTH / fa.tx : NTH / 6;   // 6 halo cells per segment, one per thread
-        const long long nseg = (long long)g.ny * g.nz * fa.spr;
-        const size_t shm = (size_t)NQ * fa.rpb * (fa.tx + 6) * sizeof(T);
-        e.template launch<BAdvFaceXRow<T, NQ>>(MHD_K_ADV_FACE, (int)((nseg + fa.rpb - 1) / fa.rpb), shm, fa);
-    }
+    typename BAdvFaceMarchY<T, NQ>::Args ma;
+    ma.g = b->g;
+    ma.U = cview(in);
+    ma.a = a;
+    ma.F = reinterpret_cast<T*>(b->F[1]);
+    ma.seg = b->seg_ay;
+    long long threads = (long long)b->g.nx * b->g.nz * ((b->g.ny + ma.seg - 1) / ma.seg);
+    e.template launch<BAdvFaceMarchY<T, NQ>>(MHD_K_ADV_FACE, (int)((threads + NTH - 1) / NTH), 0, ma);
 }
-
 
 // the two field-group launches of the fused ADV update with blocks of NT
 // threads (dynamic LDS: 2 x (NV + 2 NQ) x NT values)
@@ -663,71 +636,35 @@ void emit_adv_xz(Emit& e, const AdvXZArgs<T>& xa, int blocks, bool ion)
     else e.template launch<BAdvXZUpdate<T, 4, 3, NT>>(MHD_K_ADV_UPDATE, blocks, shm(5, 3), xa);
 }
 
-// tail: the step's last substage, whose energy-group launch runs the tail of
-// the step and leaves the CFL speed maxima in b->part
+// One ADV substage: y faces marched along y, then the update with its x and z
+// faces
 template <typename T, class Emit>
-void emit_adv_substage(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout, const StepArgs& a, RK rk, int dbg,
-                       bool tail = false)
+void emit_adv_substage(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout, const StepArgs& a, RK rk, int dbg)
 {
     Fields<T> in = view<T>(b, sin.h, sin.m, sin.b);
     Fields<T> S = view<T>(b, sS.h, sS.m, sS.b);
     Fields<T> out = view<T>(b, sout.h, sout.m, sout.b);
     const bool ion = b->p.ionisation != 0;
-    if (adv_xz(b->g, sizeof(T))) {
-        // y faces marched along y; the x faces inside the z-marching update
-        if (ion) emit_adv_face<T, 1, 8>(b, e, in, a);
-        else emit_adv_face<T, 1, 7>(b, e, in, a);
-        AdvXZArgs<T> xa;
-        xa.g = b->g;
-        xa.U = cview(in);
-        xa.S = cview(S);
-        xa.O = out;
-        xa.Fy = reinterpret_cast<T*>(b->F[1]);
-        xa.a = a;
-        xa.rk = rk;
-        xa.dbg = dbg;
-        xz_tiling(b->g, sizeof(T), xa.rpb, xa.nrg);
-        xa.seg = b->seg_xz;
-        const int nt = xz_block_threads(b->g, sizeof(T));
-        const int blocks = xa.nrg * ((b->g.nz + xa.seg - 1) / xa.seg);
-        if (nt == 256) emit_adv_xz<T, 256>(e, xa, blocks, ion);
-        else if (nt == 512) emit_adv_xz<T, 512>(e, xa, blocks, ion);
-        else if constexpr (sizeof(T) == 4) emit_adv_xz<T, 1024>(e, xa, blocks, ion);
-        return;
+    if (ion) emit_adv_face<T, 8>(b, e, in, a);
+    else emit_adv_face<T, 7>(b, e, in, a);
+    AdvXZArgs<T> xa;
+    xa.g = b->g;
+    xa.U = cview(in);
+    xa.S = cview(S);
+    xa.O = out;
+    xa.Fy = reinterpret_cast<T*>(b->F[1]);
+    xa.a = a;
+    xa.rk = rk;
+    xa.dbg = dbg;
+    const bool wide = wide_rows(b->g, sizeof(T));
+    xa.rt = row_tile(b->g.nx, wide ? 512 : ROW_NT);
+    xa.nrg = (int)(((long long)b->g.ny * xa.rt.spr + xa.rt.rpb - 1) / xa.rt.rpb);
+    xa.seg = b->seg_xz;
+    const int blocks = xa.nrg * ((b->g.nz + xa.seg - 1) / xa.seg);
+    if constexpr (sizeof(T) == 4) {
+        if (wide) emit_adv_xz<T, 512>(e, xa, blocks, ion);
     }
-    // x faces from staged row segments, one face per thread; y faces marched
-    // along y, each cell's parabola formed once
-    if (ion) {
-        emit_adv_face<T, 0, 8>(b, e, in, a);
-        emit_adv_face<T, 1, 8>(b, e, in, a);
-    } else {
-        emit_adv_face<T, 0, 7>(b, e, in, a);
-        emit_adv_face<T, 1, 7>(b, e, in, a);
-    }
-    // z faces marched together with the update of every cell
-    AdvZArgs<T> ua;
-    ua.g = b->g;
-    ua.U = cview(in);
-    ua.S = cview(S);
-    ua.O = out;
-    ua.Fx = reinterpret_cast<T*>(b->F[0]);
-    ua.Fy = reinterpret_cast<T*>(b->F[1]);
-    ua.a = a;
-    ua.rk = rk;
-    ua.dbg = dbg;
-    ua.zt = ztile_of(b->g, NTH);
-    ua.ch = chem_args(b);
-    ua.part = b->part;
-    ua.flags = b->flags;
-    const int blocks = ztile_blocks(b->g, ua.zt);
-    e.template launch<BAdvZUpdate<T, 0, 4>>(MHD_K_ADV_UPDATE, blocks, 0, ua);   // rho, m
-    if (b->p.ionisation) {
-        if (tail) e.template launch<BAdvZUpdate<T, 4, 4, true>>(MHD_K_ADV_UPDATE, blocks, 0, ua);
-        else e.template launch<BAdvZUpdate<T, 4, 4>>(MHD_K_ADV_UPDATE, blocks, 0, ua);   // E, e, h2, hp
-    } else {
-        if (tail) e.template launch<BAdvZUpdate<T, 4, 3, true>>(MHD_K_ADV_UPDATE, blocks, 0, ua);
-        else e.template launch<BAdvZUpdate<T, 4, 3>>(MHD_K_ADV_UPDATE, blocks, 0, ua);   // E, e, h2
-    }
+    if (!wide) emit_adv_xz<T, ROW_NT>(e, xa, blocks, ion);
 }
 
 // NONADV stage: the M and B groups each rotate through their three slots
@@ -747,9 +684,8 @@ void emit_nonadv_stage(mhd_box* b, Emit& e, const StepArgs& a, bool first)
 }
 
 // ADV stage: the H and M groups rotate; B is read from its current slot
-// tail: run the tail of the step inside the last substage (the step itself)
 template <typename T, class Emit>
-void emit_adv_stage(mhd_box* b, Emit& e, const StepArgs& a, bool tail = false)
+void emit_adv_stage(mhd_box* b, Emit& e, const StepArgs& a)
 {
     int Sh = b->cur[GH], Sm = b->cur[GM], bb = b->cur[GB];
     Slots S0 = { Sh, Sm, bb };
@@ -757,7 +693,7 @@ void emit_adv_stage(mhd_box* b, Emit& e, const StepArgs& a, bool tail = false)
     Slots B2 = { (Sh + 2) % 3, (Sm + 2) % 3, bb };
     emit_adv_substage<T>(b, e, S0, S0, A, a, rk_coef[0], 0);
     emit_adv_substage<T>(b, e, A, S0, B2, a, rk_coef[1], 0);
-    emit_adv_substage<T>(b, e, B2, S0, A, a, rk_coef[2], 0, tail);
+    emit_adv_substage<T>(b, e, B2, S0, A, a, rk_coef[2], 0);
     b->cur[GH] = A.h;
     b->cur[GM] = A.m;
 }
@@ -880,17 +816,8 @@ void emit_step(mhd_box* b, Emit& e, const StepArgs& a)
 {
     if (b->grav) emit_poisson<T>(b, e);
     emit_nonadv_stage<T>(b, e, a, true);
-    if (adv_xz(b->g, sizeof(T))) {
-        // the fused ADV update forms x faces at every plane; with the tail's
-        // FP64 chemistry on top it would spill, so the tail is a pass of its
-        // own (the same arithmetic)
-        emit_adv_stage<T>(b, e, a, false);
-        emit_tail<T>(b, e, a, 1);
-    } else {
-        // the tail of the step runs inside the last ADV launch
-        emit_adv_stage<T>(b, e, a, true);
-        emit_reduce_dt(b, e, ztile_blocks(b->g, ztile_of(b->g, NTH)));
-    }
+    emit_adv_stage<T>(b, e, a);
+    emit_tail<T>(b, e, a, 1);
 }
 
 // ---------------------------------------------------------------- single-box operations
@@ -1526,12 +1453,7 @@ int mhd_conserved_totals_noalloc(const void* state, int32_t precision, const int
     double* part = nullptr;
     int st = scratch_of_current_device(&part);
     if (st) return st;
-    Geo g;
-    g.nx = n[0];
-    g.ny = n[1];
-    g.nz = n[2];
-    g.nxy = n[0] * n[1];
-    g.n = (int)cells;
+    const Geo g = make_geo(n[0], n[1], n[2]);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     return precision == MHD_FP64 ? totals_noalloc<double>(state, g, s, part, out)
                                  : totals_noalloc<float>(state, g, s, part, out);

@@ -94,6 +94,53 @@ __device__ __forceinline__ bool ztile_cell(const Geo& g, const ZTile& z, int blk
     return ly < z.ty && i < g.nx && j < g.ny && k0 < g.nz;
 }
 
+// Row segments of the kernels that exchange cells along x through LDS.  A
+// block stages rpb segments of w cells, one cell per thread: whole rows where
+// one segment spans the row (spr == 1, w == nx), else tx cells, then the three
+// cells of the periodic row after them and the three before them (w == tx +
+// 6), which the faces of the tx cells need.  In either order the cell at
+// offset m is at position p + m modulo w, and own cells start on a lane that
+// a load of the row can be aligned with.  Segment n of the box is piece n % spr
+// of row n / spr.
+struct RowTile {
+    int tx, spr, w, rpb;
+    FastDiv dspr, dw;
+};
+
+// the staged cell of a thread: position p in its segment, its x index and row;
+// `live` threads hold a cell, `own` ones one that the segment itself covers.
+// at(m): the thread that stages the cell at offset m along x (from a halo
+// cell possibly another one, whose values go nowhere).
+struct RowCell {
+    int p, i, row, first, w;
+    bool live, own;
+    __device__ __forceinline__ int at(int m) const   // |m| <= 3
+    {
+        if (w < 3) return first + wrapc(p + m, w);
+        const unsigned t = (unsigned)(p + m);   // of t and t -+ w the one in [0, w) is the smaller unsigned
+        return first + (int)min(t, m < 0 ? t + w : t - w);
+    }
+};
+
+__device__ __forceinline__ RowCell row_cell(const Geo& g, const RowTile& t, int rows, int blk, int tid)
+{
+    RowCell c;
+    const int r = t.dw.div(tid);
+    c.w = t.w;
+    c.first = r * t.w;
+    c.p = tid - c.first;
+    const int n = blk * t.rpb + r;
+    c.row = t.dspr.div(n);
+    c.live = c.own = r < t.rpb && c.row < rows;
+    c.i = c.p;
+    if (t.spr != 1) {
+        const int x = (n - c.row * t.spr) * t.tx + (c.p < t.tx + 3 ? c.p : c.p - t.w);
+        c.i = wrapc(x, g.nx);
+        c.own = c.live && c.p < t.tx && x < g.nx;
+    }
+    return c;
+}
+
 // occupancy floor: a body may ask for at least MINW waves per SIMD (the
 // compiler then caps its registers); default 1
 template <class Body, class = void> struct MinWaves { static constexpr int v = 1; };
@@ -232,7 +279,7 @@ struct FaceArgs {
     CFields<T> U;            // substage input state
     T* F;
     StepArgs a;
-    int rpb;                 // x rows per block (row kernel)
+    RowTile rt;              // row segments (row kernel)
     int seg;                 // faces per thread (marching kernel)
     uint32_t* flags;
     const double* dt_cfl;    // non-null: check the explicit dt against this CFL bound
@@ -257,56 +304,6 @@ __device__ __forceinline__ void check_dt(const FaceArgs<T>& A, int blk, int tid)
         atomicOr(A.flags, 2u);
 }
 
-// NONADV faces along D, one face per thread, both adjacent parabolas computed
-// by the thread from the primitives of the six cells of its line (general
-// fallback for any box)
-template <typename T, int D, bool ION>
-struct BFacePair {
-    static constexpr int NT = NTH;
-    static constexpr bool XCD = false;
-    using Args = FaceArgs<T>;
-    static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
-    {
-        const Geo& g = A.g;
-        check_dt(A, blk, tid);
-        int c = blk * NT + tid;
-        if (c >= g.n) return;
-        constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
-        int i, j, k;
-        decompose(g, c, i, j, k);
-        const size_t N = (size_t)g.n;
-        // the cells of the line share their transverse coordinates, so their
-        // upper transverse neighbours sit at the same offsets
-        const int o1 = nbr<T1>(g, c, i, j, k, 1) - c, o2 = nbr<T2>(g, c, i, j, k, 1) - c;
-        T q[6][6], rho[6], gam[6];
-#pragma unroll
-        for (int m = 0; m < 6; m++) {
-            int cm = nbr<D>(g, c, i, j, k, m - 3);
-            Raw<T> rw;
-            raw_load<T, D, ION>(A.U, cm, cm + o1, cm + o2, rw);
-            T qm[6];
-            raw_prim<T, ION>(rw, A.a.gamma, qm, gam[m]);
-#pragma unroll
-            for (int v = 0; v < 6; v++) q[v][m] = qm[v];
-            rho[m] = rw.rho;
-        }
-        Side<T> L, R;
-#pragma unroll
-        for (int v = 0; v < 6; v++) {
-            Par<T> PL, PR;
-            parabola_pair(q[v][0], q[v][1], q[v][2], q[v][3], q[v][4], q[v][5], PL, PR);
-            side_left(PL, L, v);
-            side_right(PR, R, v);
-        }
-        T out[7];
-        const T gm = T(A.a.gamma);
-        face_solve(rho[2], q[5][2], q[3][2], q[4][2], rho[3], q[5][3], q[3][3], q[4][3], A.U.f[BX + D][c], L, R,
-                   gm, gam[2], gam[3], ION, T(A.a.theta * (step_dt(A.a) / A.a.h)), root_nr(rho[2]), root_nr(rho[3]),
-                   out);
-        store_face(A.F, N, c, out);
-    }
-};
-
 // The y and z face kernels store, for FP32 state, the per-cell difference of
 // the five fluxes between a cell's upper and lower face (what the update
 // reads) instead of the face values, so the update reads one value per flux;
@@ -314,11 +311,11 @@ struct BFacePair {
 // the carried fluxes would not fit the marching kernel's registers.)
 template <typename T> struct FluxDiff { static constexpr bool v = sizeof(T) == 4; };
 
-// NONADV faces along x with whole x rows per block, fused with the update of
-// m, E and e.  Each thread owns one cell, forms its primitives and computes,
+// NONADV faces along x with row segments per block (RowTile), fused with the
+// update of m, E and e.  Each thread owns one cell, forms its primitives and computes,
 // once each, its limited slopes, the interface values at its lower face and
 // its parabolas (Sec. 2.1); neighbours' primitives, slopes, interface values
-// and parabola sides come through LDS (periodic wrap inside the row).  After
+// and parabola sides come through LDS.  After
 // the face solve the row's x-face fluxes are exchanged the same way, so the
 // thread forms the flux differences of its cell (y and z faces from the face
 // kernels that ran before), the p dV work, the gravity sources and the
@@ -336,14 +333,10 @@ template <typename T, int MAXT, bool ION>
 struct BFaceXRows {
     static constexpr int NT = MAXT;
     static constexpr bool XCD = false;
-    // FP64 rows of 512 cells: two blocks per CU (72 KB of LDS each) need four
-    // waves per SIMD, i.e. at most 128 registers; the few values that spill
-    // cost less than the waiting of a single block at its barriers
-    static constexpr int MINW = (MAXT == 512 && sizeof(T) == 8) ? 4 : 1;
-    // FP32 256-thread rows keep one workgroup per tile in the persistent
-    // multi-box form: the tile loop costs three registers (83 instead of 80),
-    // five waves per SIMD instead of six, and these small tiles run 8%
-    // slower (held to six waves, the spills cost more)
+    // FP32 rows keep one workgroup per tile in the persistent multi-box form:
+    // the tile loop costs three registers (83 instead of 80), five waves per
+    // SIMD instead of six, and these small tiles run 8% slower (held to six
+    // waves, the spills cost more)
     static constexpr bool PERSIST = !(MAXT == 256 && sizeof(T) == 4);
     using Args = FaceArgs<T>;
     // LDS slot of edge value k (qL, qR) of variable v's published parabola:
@@ -360,67 +353,37 @@ struct BFaceXRows {
         const size_t N = (size_t)g.n;
         const int nx = g.nx;
         check_dt(A, blk, tid);
-        // one row per block: rows in XCD bands, so the next row's and the next
-        // plane's y and z fluxes are mostly read through this XCD's L2 (a fifth
-        // of the reads fewer, about 1% slower).  Only then are the row indices
-        // the block indices: with several rows per block the band's domain
-        // (ny nz) would exceed the blocks
-        if (A.rpb == 1) blk = xcd_band(blk, 1, g.ny, g.nz);
-        // row r of the block, cell i of the row (one row per block: no
-        // per-thread division)
-        int r, i;
-        if (nx == NT) {
-            r = 0;
-            i = tid;
-        } else {
-            r = tid / nx;
-            i = tid - r * nx;
-        }
-        const int row = blk * A.rpb + r;
-        // the row's y and z indices: with rows of a multiple of 64 cells each
-        // wave lies in one row and divides once, on the scalar unit (unsigned
-        // there, so that the compiler does not merge the two divisions into
-        // one per-thread division after the branch)
-        int j, k;
-        if ((nx & 63) == 0) {
-            const unsigned wrow = (unsigned)__builtin_amdgcn_readfirstlane(row);
-            j = (int)(wrow % (unsigned)g.ny);
-            k = (int)(wrow / (unsigned)g.ny);
-        } else {
-            j = row % g.ny;
-            k = row / g.ny;
-        }
-        bool act = r < A.rpb && row < g.ny * g.nz;
-        const int rowbase = row * nx;
-        const int c = rowbase + i;
-        const int rb = r * nx;
-        const int tl = rb + (i == 0 ? nx - 1 : i - 1);   // thread of the left cell
-        const int tr = rb + (i + 1 == nx ? 0 : i + 1);   // thread of the right cell
-        const int tm2 = rb + wrapc(i - 2, nx), tp2 = rb + wrapc(i + 2, nx);
+        // one segment per block: rows in XCD bands, so the next row's and the
+        // next plane's y and z fluxes are mostly read through this XCD's L2 (a
+        // fifth of the reads fewer, about 1% slower).  Only then are the row
+        // indices the block indices: with several segments per block the
+        // band's domain (spr ny nz) would exceed the blocks
+        if (A.rt.rpb == 1) blk = xcd_band(blk, A.rt.spr, g.ny, g.nz);
+        const RowCell rc = row_cell(g, A.rt, g.ny * g.nz, blk, tid);
+        const int k = g.dy.div(rc.row), j = rc.row - k * g.ny;
+        const int c = rc.row * nx + rc.i;
+        const int tl = rc.at(-1), tr = rc.at(1);   // threads of the left and right cells
+        const int tm2 = rc.at(-2), tp2 = rc.at(2);
         const T gm = T(A.a.gamma);
         // periodic offsets of the upper neighbours along y and z
         const int dyp = ((j + 1 == g.ny ? 0 : j + 1) - j) * nx;
         const int dzp = ((k + 1 == g.nz ? 0 : k + 1) - k) * g.nxy;
         // the step's dt (device-resident under the CFL step), read before any
         // store of this kernel: read later, each wave would wait for the load
-        // after a barrier, with every other wave of the block (FP64 rows of
-        // 512 cells, held to 128 registers, read it where it is used: the
-        // two registers would spill)
-        constexpr bool DT_EARLY = !(sizeof(T) == 8 && MAXT == 512);
-        const double dt_early = DT_EARLY ? step_dt(A.a) : 0.0;
-        auto dt_now = [&]() { return DT_EARLY ? dt_early : step_dt(A.a); };
+        // after a barrier, with every other wave of the block
+        const double dt_now = step_dt(A.a);
 
         // own cell: conserved values, primitives
         // uc, sc: the cell's m, E, e at the substage input and at the stage
         // start, for the update at the end.  With EARLY they are taken here
-        // (FP64 rows of 256 cells: the registers still fit three waves per
-        // SIMD, and the stores of the face outputs in between would make the
-        // compiler load them again); otherwise loaded at the update (FP32
-        // would drop from six to five waves, the 512-cell rows would spill)
-        constexpr bool EARLY = sizeof(T) == 8 && MAXT == 256;
+        // (FP64: the registers still fit three waves per SIMD, and the stores
+        // of the face outputs in between would make the compiler load them
+        // again); otherwise loaded at the update (FP32 would drop from six to
+        // five waves)
+        constexpr bool EARLY = sizeof(T) == 8;
         T q2[6], rho = T(0), gam = gm, bn = T(0), srho = T(0), uc[5], sc[5];
         const int upd[5] = { MX, MY, MZ, EN, EI };
-        if (act) {
+        if (rc.live) {
             Raw<T> rw;
             raw_load<T, 0, ION>(A.U, c, c + dyp, c + dzp, rw);
             bn = A.U.f[BX][c];
@@ -447,7 +410,7 @@ struct BFaceXRows {
         // gamma); slopes of the own cell
         T q0[6], q1[6], q3[6], q4[6], dm[6], fl[6];
         T rl = T(0), gl = gm, srl = T(0);
-        if (act) {
+        if (rc.live) {
 #pragma unroll
             for (int v = 0; v < 6; v++) {
                 q0[v] = sm[v * NT + tm2];
@@ -472,7 +435,7 @@ struct BFaceXRows {
         // primitives, densities and gamma there are no longer read; the
         // slopes in 8-13 are read until the barrier below)
         Side<T> R;
-        if (act) {
+        if (rc.live) {
 #pragma unroll
             for (int v = 0; v < 6; v++) {
                 fl[v] = interface_value(q1[v], q2[v], sm[(8 + v) * NT + tl], dm[v]);
@@ -490,31 +453,11 @@ struct BFaceXRows {
         // the update's y and z flux values (per-cell differences when the
         // marches stored them) and, without EARLY, its m, E, e inputs: loaded
         // after the face solve, before this thread's stores (outputs may alias
-        // inputs as far as the compiler knows) and, with LOADS_AHEAD, before
-        // the barrier, so their latency overlaps the wait (FP64 rows of 512
-        // cells, held to 128 registers, would spill more: they load after it)
+        // inputs as far as the compiler knows) and before the barrier, so
+        // their latency overlaps the wait
         constexpr bool DIFF = FluxDiff<T>::v;
-        constexpr bool LOADS_AHEAD = !(sizeof(T) == 8 && MAXT == 512);
         T fy[5], fz[5], fyp[DIFF ? 1 : 5], fzp[DIFF ? 1 : 5];
-        auto load_update_inputs = [&]() {
-#pragma unroll
-            for (int v = 0; v < 5; v++) {
-                fy[v] = A.Fy[v * N + c];
-                fz[v] = A.Fz[v * N + c];
-                if constexpr (!DIFF) {
-                    fyp[v] = A.Fy[v * N + c + dyp];
-                    fzp[v] = A.Fz[v * N + c + dzp];
-                }
-            }
-            if constexpr (!EARLY) {
-#pragma unroll
-                for (int q = 0; q < 5; q++) {
-                    uc[q] = A.U.f[upd[q]][c];
-                    sc[q] = A.S.f[upd[q]][c];
-                }
-            }
-        };
-        if (act) {
+        if (rc.live) {
             // the left cell's right side (Step 5 of parabola_finish on its
             // edge values and its mean q1)
             Side<T> L;
@@ -527,20 +470,36 @@ struct BFaceXRows {
             }
             // parabola variables 3, 4, 5 are Bt1, Bt2, p
             face_solve(rl, q1[5], q1[3], q1[4], rho, q2[5], q2[3], q2[4], bn, L, R, gm, gl, gam, ION,
-                       T(A.a.theta * (dt_now() / A.a.h)), srl, srho, out);
-            if constexpr (LOADS_AHEAD) load_update_inputs();
-            A.F[5 * N + c] = out[5];
-            A.F[6 * N + c] = out[6];
+                       T(A.a.theta * (dt_now / A.a.h)), srl, srho, out);
+            if (rc.own) {
+#pragma unroll
+                for (int v = 0; v < 5; v++) {
+                    fy[v] = A.Fy[v * N + c];
+                    fz[v] = A.Fz[v * N + c];
+                    if constexpr (!DIFF) {
+                        fyp[v] = A.Fy[v * N + c + dyp];
+                        fzp[v] = A.Fz[v * N + c + dzp];
+                    }
+                }
+                if constexpr (!EARLY) {
+#pragma unroll
+                    for (int q = 0; q < 5; q++) {
+                        uc[q] = A.U.f[upd[q]][c];
+                        sc[q] = A.S.f[upd[q]][c];
+                    }
+                }
+                A.F[5 * N + c] = out[5];
+                A.F[6 * N + c] = out[6];
+            }
 #pragma unroll
             for (int v = 0; v < 5; v++) sm[(8 + v) * NT + tid] = out[v];
         }
         __syncthreads();
-        if (!act) return;
-        if constexpr (!LOADS_AHEAD) load_update_inputs();
+        if (!rc.own) return;
 
         // update of m, E, e: flux differences of the x faces (the right
         // cell's lower face from LDS), y and z faces (loaded above)
-        const T dtdx = T(dt_now() / A.a.h);
+        const T dtdx = T(dt_now / A.a.h);
         T dF[3][5];
 #pragma unroll
         for (int v = 0; v < 5; v++) {
@@ -568,8 +527,8 @@ struct BFaceXRows {
             // m and -m . grad(Phi) on E, central differences
             const T* ph = A.phi;
             const T i2h = T(0.5 / A.a.h);
-            const T dt = T(dt_now());
-            const int dxp = tr - tid, dxm = tl - tid;
+            const T dt = T(dt_now);
+            const int dxp = (rc.i + 1 == nx ? 0 : rc.i + 1) - rc.i, dxm = (rc.i == 0 ? nx - 1 : rc.i - 1) - rc.i;
             const int dym = ((j == 0 ? g.ny - 1 : j - 1) - j) * nx;
             const int dzm = ((k == 0 ? g.nz - 1 : k - 1) - k) * g.nxy;
             T gv[3] = { (ph[c + dxp] - ph[c + dxm]) * i2h, (ph[c + dyp] - ph[c + dym]) * i2h,
@@ -615,11 +574,9 @@ struct BFaceMarch {
         const int nd = D == 1 ? g.ny : g.nz;
         const int no = D == 1 ? g.nz : g.ny;
         const int nseg = (nd + seg - 1) / seg;
-        int t = blk * NT + tid;
-        int i = t % g.nx;
-        int rest = t / g.nx;
-        int o = rest % no;
-        int sgi = rest / no;
+        const int t = blk * NT + tid;
+        const int rest = g.dx.div(t), i = t - rest * g.nx;
+        const int sgi = (D == 1 ? g.dz : g.dy).div(rest), o = rest - sgi * no;
         if (sgi >= nseg) return;
         const int base = D == 1 ? i + g.nxy * o : i + g.nx * o;
         const int stride = D == 1 ? g.nx : g.nxy;
@@ -762,15 +719,14 @@ struct BFaceMarch {
     }
 };
 
-// NONADV update: flux differences, p dV work, face-field update from edge
-// fields (Sec. 2.5), Runge-Kutta combination (Sec. 2.2).  dbg != 0 writes
-// tau R(U) instead of the combination.  Each thread marches along z over a
-// segment of cells (ZTile); the Ex, Ey on the upper z edges of cell k, the
-// edge-field components they read, and (full update, FP64) the z-face fluxes
-// at its upper face are the lower ones of cell k+1, so they are carried
-// instead of read or formed again (same arithmetic).
+// Face-field update from edge fields (Sec. 2.5) with its Runge-Kutta
+// combination (Sec. 2.2), after the x-row face kernel has updated m, E and e.
+// dbg != 0 writes tau R(U) instead of the combination.  Each thread marches
+// along z over a segment of cells (ZTile); the Ex, Ey on the upper z edges of
+// cell k and the edge-field components they read are the lower ones of cell
+// k+1, so they are carried instead of read or formed again (same arithmetic).
 template <typename T>
-struct NonadvUpdateArgs {
+struct FieldUpdateArgs {
     Geo g;
     CFields<T> U, S;
     Fields<T> O;
@@ -781,23 +737,19 @@ struct NonadvUpdateArgs {
     RK rk;
     int dbg;
     ZTile zt;
-    const T* phi;   // gravitational potential, or null without self-gravity
 };
 
-// threads per block of the NONADV update and the x width of its x-y tile
+// threads per block of the face-field update and the x width of its x-y tile
 // (UPD_TX x UPD_NT / UPD_TX cells)
 constexpr int UPD_NT = 256;
 constexpr int UPD_TX = 64;
 
-// FULL: all eight fields (the update of boxes whose x faces come from the
-// one-face-per-thread kernel); otherwise only the face fields b_x, b_y, b_z,
-// after the x-row face kernel has updated m, E and e
-template <typename T, bool ION, bool FULL>
-struct BNonadvUpdate {
+template <typename T>
+struct BFieldUpdate {
     static constexpr int NT = UPD_NT;
     static constexpr bool XCD = false;
-    static constexpr int MINW = ION ? 1 : 4;
-    using Args = NonadvUpdateArgs<T>;
+    static constexpr int MINW = 4;
+    using Args = FieldUpdateArgs<T>;
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
     {
         const Geo& g = A.g;
@@ -829,20 +781,14 @@ struct BNonadvUpdate {
         const T* exz = Fx + 6 * N;   // x faces, E along z
         auto Ez = [&](int cc, int cym, int cxm) { return T(0.25) * (((exz[cym] + exz[cc]) + eyz[cxm]) + eyz[cc]); };
 
-        // carried from the cell below: the z-face values at the lower face of
-        // the current cell, the Ex, Ey on its lower z edges, and the face
+        // carried from the cell below: the Ex, Ey on its lower z edges, and the face
         // edge-field values of the current plane (and of the plane below at
         // x+1, y+1) that the cell below read as its upper-plane values
-        T fzc[5];
         T Ex_c, Ey_c;
         T ezx_c, eyx_c, ezy_c, exy_c, eyx_ypm, exy_xpm;
         {
             int c = i + nx * j + nxy * k0;
             int zm = c + ((k0 == 0 ? nz - 1 : k0 - 1) - k0) * nxy;
-            if (FULL && !FluxDiff<T>::v) {
-#pragma unroll
-                for (int v = 0; v < 5; v++) fzc[v] = Fz[v * N + c];
-            }
             ezx_c = ezx[c];
             eyx_c = eyx[c];
             ezy_c = ezy[c];
@@ -860,69 +806,16 @@ struct BNonadvUpdate {
         for (int k = k0; k < k1; k++) {
             const int c = i + nx * j + nxy * k;
             const int dzp = ((k + 1 == nz ? 0 : k + 1) - k) * nxy;
-            const int dzm = ((k == 0 ? nz - 1 : k - 1) - k) * nxy;
             const int xp = c + dxp, xm = c + dxm, yp = c + dyp, ym = c + dym, zp = c + dzp;
-            constexpr int Q0 = FULL ? 0 : 5;
-            const int upd[8] = { MX, MY, MZ, EN, EI, BX, BY, BZ };
             // the face fields' Runge-Kutta inputs, all loaded before the
             // plane's stores (a load issued after a store waits for the store
-            // as well: one memory counter, in order); the full update, with
-            // eight fields, keeps them at the combination (here it would
-            // spill)
-            T uo[8], so[8];
-            if (!FULL && !A.dbg) {
+            // as well: one memory counter, in order)
+            T uo[3], so[3], inc[3];
+            if (!A.dbg) {
 #pragma unroll
-                for (int q = Q0; q < 8; q++) {
-                    uo[q] = A.U.f[upd[q]][c];
-                    so[q] = A.S.f[upd[q]][c];
-                }
-            }
-            T inc[NF];
-            if (FULL) {
-                T dF[3][5], fzp[5];
-#pragma unroll
-                for (int v = 0; v < 5; v++) {
-                    dF[0][v] = Fx[v * N + xp] - Fx[v * N + c];
-                    if (FluxDiff<T>::v) {   // the marches stored per-cell differences
-                        dF[1][v] = Fy[v * N + c];
-                        dF[2][v] = Fz[v * N + c];
-                    } else {
-                        dF[1][v] = Fy[v * N + yp] - Fy[v * N + c];
-                        fzp[v] = Fz[v * N + zp];
-                        dF[2][v] = fzp[v] - fzc[v];
-                    }
-                }
-                // momentum component a takes slot (a - d) mod 3 from direction d
-                inc[MX] = -dtdx * ((dF[0][0] + dF[1][2]) + dF[2][1]);
-                inc[MY] = -dtdx * ((dF[0][1] + dF[1][0]) + dF[2][2]);
-                inc[MZ] = -dtdx * ((dF[0][2] + dF[1][1]) + dF[2][0]);
-                inc[EN] = -dtdx * ((dF[0][3] + dF[1][3]) + dF[2][3]);
-                T divv = (dF[0][4] + dF[1][4]) + dF[2][4];
-                // with the network, gamma_eff of the cell (FP64, as the tail forms it)
-                T gm1 = T(A.a.gamma - 1.0);
-                if (ION)
-                    gm1 = T(gamma_cell(1, 0.0, (double)A.U.f[RHO][c], (double)A.U.f[H2][c], (double)A.U.f[HP][c])) -
-                          T(1);
-                inc[EI] = -gm1 * A.U.f[EI][c] * dtdx * divv;
-                if (A.phi) {
-                    // self-gravity (Sec. 2 equations, Sec. 2.4): -rho grad(Phi) on
-                    // m and -m . grad(Phi) on E, central differences
-                    const T* ph = A.phi;
-                    const T i2h = T(0.5 / A.a.h);
-                    const T dt = T(step_dt(A.a));
-                    T gv[3] = { (ph[xp] - ph[xm]) * i2h, (ph[yp] - ph[ym]) * i2h, (ph[zp] - ph[c + dzm]) * i2h };
-                    T rho = A.U.f[RHO][c];
-                    T work = T(0);
-#pragma unroll
-                    for (int a = 0; a < 3; a++) {
-                        inc[MX + a] -= dt * rho * gv[a];
-                        work += A.U.f[MX + a][c] * gv[a];
-                    }
-                    inc[EN] -= dt * work;
-                }
-                if (!FluxDiff<T>::v) {
-#pragma unroll
-                    for (int v = 0; v < 5; v++) fzc[v] = fzp[v];
+                for (int q = 0; q < 3; q++) {
+                    uo[q] = A.U.f[BX + q][c];
+                    so[q] = A.S.f[BX + q][c];
                 }
             }
 
@@ -937,27 +830,16 @@ struct BNonadvUpdate {
             T Ez_c = Ez(c, ym, xm);
             T Ez_xp = Ez(xp, xp + dym, c);
             T Ez_yp = Ez(yp, c, yp + dxm);
-            inc[BX] = -dtdx * (Ez_yp - Ez_c) + dtdx * (Ey_zp - Ey_c);
-            inc[BY] = -dtdx * (Ex_zp - Ex_c) + dtdx * (Ez_xp - Ez_c);
-            inc[BZ] = -dtdx * (Ey_xp - Ey_c) + dtdx * (Ex_yp - Ex_c);
+            inc[0] = -dtdx * (Ez_yp - Ez_c) + dtdx * (Ey_zp - Ey_c);
+            inc[1] = -dtdx * (Ex_zp - Ex_c) + dtdx * (Ez_xp - Ez_c);
+            inc[2] = -dtdx * (Ey_xp - Ey_c) + dtdx * (Ex_yp - Ex_c);
 
             if (A.dbg) {
 #pragma unroll
-                for (int q = Q0; q < 8; q++) A.O.f[upd[q]][c] = inc[upd[q]];
-                if (FULL) {
-                    A.O.f[RHO][c] = T(0);
-                    A.O.f[H2][c] = T(0);
-                    if (ION) A.O.f[HP][c] = T(0);   // H+ is a field of its own only with the network
-                }
+                for (int q = 0; q < 3; q++) A.O.f[BX + q][c] = inc[q];
             } else {
 #pragma unroll
-                for (int q = Q0; q < 8; q++) {
-                    if constexpr (FULL) {
-                        uo[q] = A.U.f[upd[q]][c];
-                        so[q] = A.S.f[upd[q]][c];
-                    }
-                    A.O.f[upd[q]][c] = (uo[q] + ra * (so[q] - uo[q])) + rb * inc[upd[q]];
-                }
+                for (int q = 0; q < 3; q++) A.O.f[BX + q][c] = (uo[q] + ra * (so[q] - uo[q])) + rb * inc[q];
             }
             Ex_c = Ex_zp;
             Ey_c = Ey_zp;
@@ -1241,92 +1123,6 @@ __device__ __forceinline__ double tail_speed(const StepArgs& a, double rho, doub
 
 // ---------------------------------------------------------------- ADV
 
-// ADV fluxes at the lower x face of every cell (Sec. 2.6): the sqrt(rho)-
-// weighted face velocity and the upwind parabola average of NQ fields (NQ =
-// 7, or 8 with the ionisation network), in the order rho, mx, my, mz, E, e,
-// h2, hp; outputs NQ x N.  A block holds rpb segments of tx cells of x rows
-// (whole rows when nx <= 256, else 256-cell pieces), each with three cells of
-// its periodic row on either side, loaded coalesced into LDS behind one
-// barrier; each thread then forms its face from the staged row, its 5-cell
-// window read at fixed offsets (no per-neighbour wrap or address
-// arithmetic).  Dynamic LDS: NQ x rpb x (tx + 6) values.
-template <typename T, int NQ>
-struct BAdvFaceXRow {
-    static constexpr int NT = NTH;
-    static constexpr bool XCD = false;
-    struct Args {
-        Geo g;
-        CFields<T> U;
-        T* F;
-        StepArgs a;
-        int tx, rpb, spr;   // segment width, segments per block, segments per row
-    };
-    static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
-    {
-        extern __shared__ unsigned char smem_raw[];
-        T* L = reinterpret_cast<T*>(smem_raw);
-        const Geo& g = A.g;
-        const int nx = g.nx, tx = A.tx, cw = tx + 6;
-        const int LS = A.rpb * cw;   // staged cells per field
-        const int nseg = g.ny * g.nz * A.spr;   // below 2^31: at most one segment per cell
-        const int fld[8] = { RHO, MX, MY, MZ, EN, EI, H2, HP };
-        // own cell
-        const int sl = tid / tx, pos = tid - sl * tx;
-        const int sg = blk * A.rpb + sl;
-        bool act = false;
-        size_t c = 0;
-        int p = 0;
-        if (sl < A.rpb && sg < nseg) {
-            const int row = sg / A.spr, s0 = (sg - row * A.spr) * tx;
-            const int w = min(tx, nx - s0);
-            if (pos < w) {
-                act = true;
-                c = (size_t)row * nx + s0 + pos;
-                p = sl * cw + pos + 3;
-#pragma unroll
-                for (int q = 0; q < NQ; q++) L[q * LS + p] = A.U.f[fld[q]][c];
-            }
-        }
-        // halo: three cells of the periodic row on each side of each segment
-        if (tid < 6 * A.rpb) {
-            const int hs = tid / 6, k = tid - 6 * hs;
-            const int hg = blk * A.rpb + hs;
-            if (hg < nseg) {
-                const int row = hg / A.spr, s0 = (hg - row * A.spr) * tx;
-                const int w = min(tx, nx - s0);
-                const int x = k < 3 ? s0 - 3 + k : s0 + w + k - 3;
-                const int hp = hs * cw + (k < 3 ? k : w + k);
-                const size_t hc = (size_t)row * nx + wrapc(x, nx);
-#pragma unroll
-                for (int q = 0; q < NQ; q++) L[q * LS + hp] = A.U.f[fld[q]][hc];
-            }
-        }
-        __syncthreads();
-        if (!act) return;
-        const T ydx = T(A.a.theta * (step_dt(A.a) / A.a.h));
-        // sqrt(rho)-weighted face velocity; sqrt(rho) v = m / sqrt(rho)
-        const T* rho = L;
-        const T* mx = L + LS;
-        const T rl = rho[p - 1], rr = rho[p];
-        const T rsl = rsqrt_nr(rl), rsr = rsqrt_nr(rr);
-        const T vf = (mx[p - 1] * rsl + mx[p] * rsr) * rcp_nr(rl * rsl + rr * rsr);
-        const bool upw = vf >= T(0);
-        const T y = upw ? ydx * vf : ydx * (-vf);
-        const int b = upw ? p - 3 : p - 2;
-        const size_t N = (size_t)g.n;
-        T out[NQ];
-#pragma unroll
-        for (int q = 0; q < NQ; q++) {
-            const T* u = L + q * LS;
-            Par<T> P = parabola(u[b], u[b + 1], u[b + 2], u[b + 3], u[b + 4]);
-            T qup = upw ? avg_right(P, y) : avg_left(P, y);
-            out[q] = vf * qup;
-        }
-#pragma unroll
-        for (int q = 0; q < NQ; q++) A.F[q * N + c] = out[q];
-    }
-};
-
 // ADV faces along y, marched: each thread walks one y line over a segment of
 // `seg` cells with a sliding 5-cell window of the NQ fields, so each cell's
 // limited slope, lower interface value and parabola are formed once (the
@@ -1360,11 +1156,9 @@ struct BAdvFaceMarchY {
         const int seg = A.seg;
         const int nd = g.ny, no = g.nz;
         const int nseg = (nd + seg - 1) / seg;
-        int t = blk * NT + tid;
-        int i = t % g.nx;
-        int rest = t / g.nx;
-        int o = rest % no;
-        int sgi = rest / no;
+        const int t = blk * NT + tid;
+        const int rest = g.dx.div(t), i = t - rest * g.nx;
+        const int sgi = g.dz.div(rest), o = rest - sgi * no;
         if (sgi >= nseg) return;
         const int base = i + g.nxy * o;
         const int stride = g.nx;
@@ -1469,51 +1263,74 @@ struct BAdvFaceMarchY {
     }
 };
 
-// ADV z faces fused with the ADV update, for the advected fields Q0 ..
-// Q0+NQ-1 of the order rho, mx, my, mz, E, e, h2, hp: each thread marches along z
-// over a segment of cells with a sliding 6-cell window of those fields, so
-// the flux at the upper z face of cell k is the lower one of cell k+1, and the
-// update reads the x and y fluxes written by the x/y face kernels.  Same
-// arithmetic as the x/y face kernels followed by a plain update.  The fields
-// are split over several launches so that a thread holds a small window and
-// more waves fit on a SIMD; every launch reads rho and mz of the two cells at
-// each face for the face velocity.
+// ADV update with its x and z faces, for the advected fields Q0 .. Q0+NQ-1 of
+// the order rho, mx, my, mz, E, e, h2, hp.  A block holds rpb row segments
+// (RowTile), one thread per column, and marches them along z over a segment
+// of cells with a sliding 6-cell window of its fields: the flux at the upper z
+// face of cell k is the lower one of cell k+1, and each cell's limited slope,
+// lower interface value and parabola along z are formed once.  At each plane
+// the threads publish their cell's values in LDS, then its limited slope, and
+// form the flux of their lower x face (sqrt(rho)-weighted velocity, the upwind
+// cell's parabola from its 5-cell window at fixed offsets); the fluxes are
+// exchanged through LDS for the x difference, so the x fluxes never pass
+// through memory; the y difference comes from memory (stored by the y march).
+// The fields are split over two launches so that a thread holds a small window
+// and more waves fit on a SIMD; both read rho and the momenta of the faces for
+// the face velocities.  Three block barriers per plane (values, slopes,
+// fluxes); the LDS is double-buffered by plane parity, so a buffer is
+// rewritten only after every thread has passed the barriers that follow its
+// last reads.  Dynamic LDS: 2 x (NV + 2 NQ) x NT values.  Threads beyond the
+// block's segments (and the segments of a last, partial group) reach every
+// barrier: they follow the first cell of the block's first segment, which is
+// always a real one, and write nothing, to LDS or memory.
 template <typename T>
-struct AdvZArgs {
+struct AdvXZArgs {
     Geo g;
     CFields<T> U, S;
     Fields<T> O;
-    const T* Fx;
     const T* Fy;
     StepArgs a;
     RK rk;
     int dbg;
-    ZTile zt;
-    // the tail of the step (TAIL launches only)
-    ChemArgs ch;
-    double* part;
-    uint32_t* flags;
+    RowTile rt; // segments of a plane's rows
+    int nrg;    // groups of rpb segments: ceil(ny * spr / rpb)
+    int seg;    // z cells per block
 };
 
-// TAIL (the field group E, e, h2 [, hp] of the step's last substage): the
-// tail of the step runs on each cell as its new values are formed (rho and m
-// are the substage's outputs of the first group, launched before; B is not
-// changed by ADV), and the block's CFL speed maximum goes to part[blk]; the
-// same arithmetic as BTail after the update.
-template <typename T, int Q0, int NQ, bool TAIL = false>
-struct BAdvZUpdate {
-    static constexpr int NT = NTH;
+template <typename T, int Q0, int NQ, int MAXT>
+struct BAdvXZUpdate {
+    static constexpr int NT = MAXT;
     static constexpr bool XCD = false;
-    static_assert(!TAIL || Q0 == 4, "the tail runs with the energy group");
-    static constexpr int MINW = TAIL ? 2 : 1;
-    static constexpr int UNROLL = TAIL ? 1 : 2;   // cells per trip of the march
-    using Args = AdvZArgs<T>;
-    // Along the march each cell's limited slope, lower interface value and
-    // parabola are formed once: for the face between window slots 2 and 3
-    // (cells k, k+1 of a window that starts at k-2) the parabola of cell k
-    // was formed at the face below (pc: its right side), and the thread forms
-    // that of cell k+1 from the carried slope d1 of cell k+1 and interface
-    // value f1 at k+1/2; the face takes the upwind average.
+    // rho and m of the cell are window fields 0-3 of the first group;
+    // the energy group stages rho and mx of the cell as two more values
+    static constexpr bool own_v = Q0 == 0 && NQ >= 4;
+    static constexpr int NV = own_v ? NQ : NQ + 2;
+    static constexpr int RI = own_v ? 0 : NQ;       // staged slot of rho
+    static constexpr int MXI = own_v ? 1 : NQ + 1;  // staged slot of mx
+    static constexpr int MINW = (sizeof(T) == 8 && Q0 == 0 && MAXT == 256) ? 3 : 1;
+    using Args = AdvXZArgs<T>;
+    static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
+    {
+        extern __shared__ unsigned char smem_raw[];
+        T* sm = reinterpret_cast<T*>(smem_raw);
+        const Geo& g = A.g;
+        const int rg = blk % A.nrg, sgi = blk / A.nrg;
+        const int k0 = sgi * A.seg, k1 = min(k0 + A.seg, g.nz);
+        RowCell rc = row_cell(g, A.rt, g.ny, rg, tid);   // segments of one plane
+        const bool live = rc.live, own = rc.own;
+        if (!live) rc = row_cell(g, A.rt, g.ny, rg, 0);
+        // threads of cells i-3 .. i+2
+        int tx[6];
+#pragma unroll
+        for (int m = 0; m < 6; m++) tx[m] = rc.at(m - 3);
+        const int tme = rc.first + rc.p;
+        march(A, sm, live, own, rc.i, rc.row, k0, k1, tx, tme);
+    }
+    // The flux at the upper z face of cell k, between window slots 2 and 3
+    // (cells k, k+1 of a window that starts at k-2): the parabola of cell k
+    // was formed at the face below (pR, pdq, p6: its right side), and the
+    // thread forms that of cell k+1 from the carried slope d1 of cell k+1 and
+    // interface value f1 at k+1/2; the face takes the upwind average.
     static __device__ __forceinline__ void zflux(const T w[NQ][6], T vf, T ydx, T pR[NQ], T pdq[NQ], T p6[NQ],
                                                  T d1[NQ], T f1[NQ], T out[NQ])
     {
@@ -1538,253 +1355,8 @@ struct BAdvZUpdate {
             f1[q] = f2;
         }
     }
-    static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
-    {
-        int i, j, x0, x1;
-        double smax = 0.0;
-        if (ztile_cell(A.g, A.zt, blk, tid, i, j, x0, x1)) march(A, i, j, x0, x1, smax);
-        if constexpr (TAIL) block_max_store(smax, A.part, blk);
-    }
-    static __device__ __forceinline__ void march(const Args& A, int i, int j, int x0, int x1, double& smax)
-    {
-        const Geo& g = A.g;
-        const int nd = g.nz;
-        const size_t N = (size_t)g.n;
-        const int base = i + g.nx * j;
-        const int stride = g.nxy;
-        const T ydx = T(A.a.theta * (step_dt(A.a) / A.a.h));
-        const T dtdx = T(step_dt(A.a) / A.a.h);
-        const int fld[8] = { RHO, MX, MY, MZ, EN, EI, H2, HP };
-        const T ra = T(A.rk.a), rb = T(A.rk.b);
-        int ip = i + 1 == g.nx ? 0 : i + 1;
-        int jp = j + 1 == g.ny ? 0 : j + 1;
-
-        // window cells z = x0-3 .. x0+2 (slots 0..5): the first face is
-        // x0-1/2.  vr, vm: rho and mz of slots 2 and 3, for the face velocity.
-        T w[NQ][6];
-        T vr[2], vm[2];
-#pragma unroll
-        for (int m = 0; m < 6; m++) {
-            int cc = base + wrapc(x0 - 3 + m, nd) * stride;
-#pragma unroll
-            for (int q = 0; q < NQ; q++) w[q][m] = A.U.f[fld[Q0 + q]][cc];
-            if (m == 2 || m == 3) {   // constant after unrolling
-                vr[m - 2] = A.U.f[RHO][cc];
-                vm[m - 2] = A.U.f[MZ][cc];
-            }
-        }
-        auto velocity = [&]() {
-            // sqrt(rho)-weighted face velocity; sqrt(rho) v = m / sqrt(rho)
-            T rsl = rsqrt_nr(vr[0]), rsr = rsqrt_nr(vr[1]);
-            return (vm[0] * rsl + vm[1] * rsr) * rcp_nr(vr[0] * rsl + vr[1] * rsr);
-        };
-        // the first face (slots 2, 3): both adjacent parabolas; then carry the
-        // upper cell's right side, the slope of the cell above it and the
-        // interface value between them
-        T Flo[NQ], pR[NQ], pdq[NQ], p6[NQ], d1[NQ], f1[NQ];
-        {
-            const T vf = velocity();
-            const bool upw = vf >= T(0);
-            const T y = upw ? ydx * vf : ydx * (-vf);
-#pragma unroll
-            for (int q = 0; q < NQ; q++) {
-                T s0 = limited_slope(w[q][0], w[q][1], w[q][2]);
-                T s1 = limited_slope(w[q][1], w[q][2], w[q][3]);
-                T s2 = limited_slope(w[q][2], w[q][3], w[q][4]);
-                T s3 = limited_slope(w[q][3], w[q][4], w[q][5]);
-                T i0 = interface_value(w[q][1], w[q][2], s0, s1);
-                T i1 = interface_value(w[q][2], w[q][3], s1, s2);
-                T i2 = interface_value(w[q][3], w[q][4], s2, s3);
-                Par<T> Pl = parabola_finish(w[q][0], w[q][1], w[q][2], w[q][3], w[q][4], i0, i1, s1);
-                Par<T> Pr = parabola_finish(w[q][1], w[q][2], w[q][3], w[q][4], w[q][5], i1, i2, s2);
-                T qup = upw ? avg_right(Pl, y) : avg_left(Pr, y);
-                Flo[q] = vf * qup;
-                pR[q] = Pr.qR;
-                pdq[q] = Pr.dq;
-                p6[q] = Pr.q6;
-                d1[q] = s3;
-                f1[q] = i2;
-            }
-        }
-        // the values cell x needs from beyond the window (cell x+3 entering
-        // it; rho and mz of cell x+1 when the group holds neither) are loaded
-        // one cell ahead, so the loads are in flight during the previous cell
-        constexpr bool own_v = Q0 == 0 && NQ >= 4;   // rho and mz are window fields 0 and 3
-        T nw[NQ], nvr = T(0), nvm = T(0);
-        auto fetch = [&](int x) {
-            int cn = base + wrapc(x + 3, nd) * stride;
-#pragma unroll
-            for (int q = 0; q < NQ; q++) nw[q] = A.U.f[fld[Q0 + q]][cn];
-            if (!own_v) {
-                int c1 = base + wrapc(x + 1, nd) * stride;
-                nvr = A.U.f[RHO][c1];
-                nvm = A.U.f[MZ][c1];
-            }
-        };
-        fetch(x0);
-        // two cells per trip halve the register moves of the window slide
-        // (measured faster here; the face marches lose by it); one with the
-        // tail, whose chemistry would double the registers
-#pragma unroll UNROLL
-        for (int x = x0; x < x1; x++) {
-            // slide: window slots 0..5 = cells x-2 .. x+3
-#pragma unroll
-            for (int q = 0; q < NQ; q++) {
-#pragma unroll
-                for (int m = 0; m < 5; m++) w[q][m] = w[q][m + 1];
-                w[q][5] = nw[q];
-            }
-            vr[0] = vr[1];
-            vm[0] = vm[1];
-            if constexpr (own_v) {
-                vr[1] = w[0][3];
-                vm[1] = w[3][3];
-            } else {
-                vr[1] = nvr;
-                vm[1] = nvm;
-            }
-            if (x + 1 < x1) fetch(x + 1);
-            // the cell's x/y flux differences and Runge-Kutta input, loaded
-            // before the z flux is formed so the loads overlap it, and before
-            // any store (the output fields may alias the inputs as far as the
-            // compiler knows)
-            int c = base + x * stride;
-            int cxp = c - i + ip;
-            int cyp = c + (jp - j) * g.nx;
-            T dx[NQ], dy[NQ], sv[NQ];
-#pragma unroll
-            for (int q = 0; q < NQ; q++) {
-                const size_t o = (size_t)(Q0 + q) * N;
-                dx[q] = A.Fx[o + cxp] - A.Fx[o + c];
-                dy[q] = A.Fy[o + c];   // the y march stored the difference
-                sv[q] = A.S.f[fld[Q0 + q]][c];
-            }
-            // the tail's inputs: the first group's new rho and m, the face
-            // field at the cell's lower and upper faces
-            T tr[4], tb[6];
-            if constexpr (TAIL) {
-                tr[0] = A.O.f[RHO][c];
-                tr[1] = A.O.f[MX][c];
-                tr[2] = A.O.f[MY][c];
-                tr[3] = A.O.f[MZ][c];
-                tb[0] = A.O.f[BX][c];
-                tb[1] = A.O.f[BX][cxp];
-                tb[2] = A.O.f[BY][c];
-                tb[3] = A.O.f[BY][cyp];
-                tb[4] = A.O.f[BZ][c];
-                tb[5] = A.O.f[BZ][c + (wrapc(x + 1, nd) - x) * stride];
-            }
-            // upper face of cell x: between slots 2 (cell x) and 3 (cell x+1)
-            T Fup[NQ], nv[NQ];
-            zflux(w, velocity(), ydx, pR, pdq, p6, d1, f1, Fup);
-#pragma unroll
-            for (int q = 0; q < NQ; q++) {
-                T dz = Fup[q] - Flo[q];
-                T inc = -dtdx * ((dx[q] + dy[q]) + dz);
-                if (A.dbg) {
-                    nv[q] = inc;
-                } else {
-                    T u = w[q][2];
-                    nv[q] = (u + ra * (sv[q] - u)) + rb * inc;
-                }
-                Flo[q] = Fup[q];
-            }
-            if constexpr (TAIL) {
-                // group fields E, e, h2 (, hp)
-                const double rho = (double)tr[0], mx = (double)tr[1], my = (double)tr[2], mz = (double)tr[3];
-                const double bx = 0.5 * ((double)tb[0] + (double)tb[1]);
-                const double by = 0.5 * ((double)tb[2] + (double)tb[3]);
-                const double bz = 0.5 * ((double)tb[4] + (double)tb[5]);
-                double E = (double)nv[0], e = (double)nv[1], h2 = (double)nv[2];
-                double hp = 0.0;
-                if constexpr (NQ > 3) hp = (double)nv[3];
-                tail_cell<T>(A.a, A.ch, rho, mx, my, mz, bx, by, bz, E, e, h2, hp);
-                nv[0] = (T)E;
-                nv[1] = (T)e;
-                nv[2] = (T)h2;
-                if constexpr (NQ > 3) nv[3] = (T)hp;
-                const double spd = tail_speed(A.a, rho, mx, my, mz, E, e, bx, by, bz, h2, hp, A.flags);
-                smax = spd > smax ? spd : smax;
-            }
-#pragma unroll
-            for (int q = 0; q < NQ; q++) A.O.f[fld[Q0 + q]][c] = nv[q];
-            if (Q0 == 0 && A.dbg) {
-                A.O.f[BX][c] = T(0);
-                A.O.f[BY][c] = T(0);
-                A.O.f[BZ][c] = T(0);
-            }
-        }
-    }
-};
-
-// ADV update with the x faces formed in the same kernel (boxes whose x rows
-// fit a block).  A block holds rpb whole x rows (nx <= NT), one thread per
-// column, and marches its rows along z over a segment of cells, like
-// BAdvZUpdate (z faces from the sliding window, y fluxes from memory, the
-// Runge-Kutta update; the tail of the step follows as a pass of its own).  At each plane the threads publish
-// their cell's values in LDS and form the flux of their lower x face exactly
-// as BAdvFaceXRow does (sqrt(rho)-weighted velocity, the upwind cell's
-// parabola from its 5-cell window at fixed row offsets, periodic inside the
-// row); the fluxes are exchanged through LDS for the x difference, so the x
-// fluxes never pass through memory.  Each cell's limited slope is formed once
-// by its own thread and shared through LDS (the per-face form computes the
-// three slopes of the upwind window from the same operands, so the results
-// are the same bits).  Three block barriers per plane (values, slopes,
-// fluxes); the LDS is double-buffered by plane parity, so a buffer is
-// rewritten only after every thread has passed the barriers that follow its
-// last reads.  Dynamic LDS: 2 x (NV + 2 NQ) x NT values.  Threads beyond the block's rows (and the rows
-// of a last, partial row group) reach every barrier: they read row 0 of the
-// block, which is always a real row, and write nothing, to LDS or memory.
-template <typename T>
-struct AdvXZArgs {
-    Geo g;
-    CFields<T> U, S;
-    Fields<T> O;
-    const T* Fy;
-    StepArgs a;
-    RK rk;
-    int dbg;
-    int rpb;    // x rows per block (nx * rpb <= NT)
-    int nrg;    // row groups: ceil(ny / rpb)
-    int seg;    // z cells per block
-};
-
-template <typename T, int Q0, int NQ, int MAXT>
-struct BAdvXZUpdate {
-    static constexpr int NT = MAXT;
-    static constexpr bool XCD = false;
-    // rho and m of the cell are window fields 0-3 of the first group;
-    // the energy group stages rho and mx of the cell as two more values
-    static constexpr bool own_v = Q0 == 0 && NQ >= 4;
-    static constexpr int NV = own_v ? NQ : NQ + 2;
-    static constexpr int RI = own_v ? 0 : NQ;       // staged slot of rho
-    static constexpr int MXI = own_v ? 1 : NQ + 1;  // staged slot of mx
-    static constexpr int MINW = (sizeof(T) == 8 && Q0 == 0 && MAXT == 256) ? 3 : 1;
-    using Args = AdvXZArgs<T>;
-    static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
-    {
-        extern __shared__ unsigned char smem_raw[];
-        T* sm = reinterpret_cast<T*>(smem_raw);
-        const Geo& g = A.g;
-        const int nx = g.nx;
-        const int r = tid / nx;
-        const int i = tid - r * nx;
-        const int rg = blk % A.nrg, sgi = blk / A.nrg;
-        const int j0 = rg * A.rpb + r;
-        const bool act = r < A.rpb && j0 < g.ny;
-        // threads beyond the rows follow a column of row 0 of the block
-        const int rr = act ? r : 0;
-        const int j = act ? j0 : rg * A.rpb;
-        const int k0 = sgi * A.seg, k1 = min(k0 + A.seg, g.nz);
-        // threads of cells i-3 .. i+2 of the row
-        int tx[6];
-#pragma unroll
-        for (int m = 0; m < 6; m++) tx[m] = rr * nx + wrapc(i + m - 3, nx);
-        const int tme = rr * nx + i;
-        march(A, sm, act, i, j, k0, k1, tx, tme);
-    }
-    static __device__ __forceinline__ void march(const Args& A, T* sm, bool act, int i, int j, int x0, int x1,
-                                                 const int tx[6], int tme)
+    static __device__ __forceinline__ void march(const Args& A, T* sm, bool live, bool own, int i, int j, int x0,
+                                                 int x1, const int tx[6], int tme)
     {
         const Geo& g = A.g;
         const int nd = g.nz;
@@ -1816,7 +1388,9 @@ struct BAdvXZUpdate {
             T rsl = rsqrt_nr(vr[0]), rsr = rsqrt_nr(vr[1]);
             return (vm[0] * rsl + vm[1] * rsr) * rcp_nr(vr[0] * rsl + vr[1] * rsr);
         };
-        // the first z face (slots 2, 3), as BAdvZUpdate
+        // the first z face (slots 2, 3): both adjacent parabolas; then carry
+        // the upper cell's right side, the slope of the cell above it and the
+        // interface value between them
         T Flo[NQ], pR[NQ], pdq[NQ], p6[NQ], d1[NQ], f1[NQ];
         {
             const T vf = velocity();
@@ -1881,7 +1455,7 @@ struct BAdvXZUpdate {
             T* vb = sm + (x & 1) * ((NV + 2 * NQ) * NT);
             T* db = vb + NV * NT;
             T* fb = db + NQ * NT;
-            if (act) {
+            if (live) {
 #pragma unroll
                 for (int q = 0; q < NQ; q++) vb[q * NT + tme] = w[q][2];
                 if constexpr (!own_v) {
@@ -1890,7 +1464,7 @@ struct BAdvXZUpdate {
                 }
             }
             __syncthreads();
-            if (act) {
+            if (live) {
 #pragma unroll
                 for (int q = 0; q < NQ; q++) {
                     const T* u = vb + q * NT;
@@ -1921,7 +1495,7 @@ struct BAdvXZUpdate {
                                                interface_value(u2, u3, dm_0, dm_p), dm_0);
                     T qup = upw ? avg_right(P, y) : avg_left(P, y);
                     fx[q] = vf * qup;
-                    if (act) fb[q * NT + tme] = fx[q];
+                    if (live) fb[q * NT + tme] = fx[q];
                 }
             }
             __syncthreads();
@@ -1940,7 +1514,7 @@ struct BAdvXZUpdate {
             }
             // upper face of cell x along z: between slots 2 and 3
             T Fup[NQ], nv[NQ];
-            BAdvZUpdate<T, Q0, NQ>::zflux(w, velocity(), ydx, pR, pdq, p6, d1, f1, Fup);
+            zflux(w, velocity(), ydx, pR, pdq, p6, d1, f1, Fup);
 #pragma unroll
             for (int q = 0; q < NQ; q++) {
                 T dx = fb[q * NT + tx[4]] - fx[q];
@@ -1954,7 +1528,7 @@ struct BAdvXZUpdate {
                 }
                 Flo[q] = Fup[q];
             }
-            if (act) {
+            if (own) {
 #pragma unroll
                 for (int q = 0; q < NQ; q++) A.O.f[fld[Q0 + q]][c] = nv[q];
                 if (Q0 == 0 && A.dbg) {
@@ -1984,8 +1558,7 @@ struct BAdvXZUpdate {
 
 // Tail of the step (after ADV) as a pass of its own: tail_cell on every cell,
 // validity flag, per-block CFL speed maximum.  mode: 1 = full tail, 0 = speed
-// only (state unchanged).  The step itself runs the tail inside its last ADV
-// launch (BAdvZUpdate with TAIL).
+// only (state unchanged).
 template <typename T>
 struct BTail {
     static constexpr int NT = NTH;
@@ -2009,18 +1582,7 @@ struct BTail {
         double spd = 0.0;
         if (c < g.n) {
             int i, j, k;
-            if ((g.nx & 63) == 0) {
-                // every wave lies in one x row: its row is divided once, on
-                // the scalar unit (signed there, so that the compiler does
-                // not merge it with the per-thread division below)
-                const int c0 = __builtin_amdgcn_readfirstlane(c);
-                const int row = c0 / g.nx;
-                j = row % g.ny;
-                k = row / g.ny;
-                i = (c0 - row * g.nx) + (c - c0);
-            } else {
-                decompose(g, c, i, j, k);
-            }
+            decompose(g, c, i, j, k);
             const Fields<T>& U = A.U;
             double rho = (double)U.f[RHO][c];
             double mx = (double)U.f[MX][c], my = (double)U.f[MY][c], mz = (double)U.f[MZ][c];

@@ -17,11 +17,45 @@ enum { RHO = 0, MX, MY, MZ, EN, EI, BX, BY, BZ, H2, HP };
 
 // ---------------------------------------------------------------- geometry
 
+// Division of 0 <= n < 2^31 by a fixed d >= 1 as one product and a shift: with
+// l = ceil(log2 d) and m = ceil(2^(31 + l) / d), n m / 2^(31 + l) exceeds n / d
+// by less than 1 / d, so its whole part is the quotient.  (The compiler's
+// division by a run-time value takes about 20 instructions.)
+struct FastDiv {
+    uint32_t m, sh;
+    __host__ __device__ __forceinline__ int div(int n) const { return (int)(((uint64_t)(uint32_t)n * m) >> sh); }
+};
+
+inline FastDiv fast_div(int d)
+{
+    uint32_t l = 0;
+    while (((uint64_t)1 << l) < (uint64_t)d) l++;
+    FastDiv f;
+    f.sh = 31 + l;
+    f.m = (uint32_t)((((uint64_t)1 << f.sh) + (uint64_t)d - 1) / (uint64_t)d);
+    return f;
+}
+
 struct Geo {
     int nx, ny, nz;
     int nxy;
     int n;          // nx * ny * nz
+    FastDiv dx, dy, dz;
 };
+
+inline Geo make_geo(int nx, int ny, int nz)
+{
+    Geo g;
+    g.nx = nx;
+    g.ny = ny;
+    g.nz = nz;
+    g.nxy = nx * ny;
+    g.n = nx * ny * nz;
+    g.dx = fast_div(nx);
+    g.dy = fast_div(ny);
+    g.dz = fast_div(nz);
+    return g;
+}
 
 __device__ __forceinline__ int wrapc(int x, int n)
 {
@@ -45,12 +79,10 @@ __device__ __forceinline__ int nbr(const Geo& g, int c, int i, int j, int k, int
 
 __device__ __forceinline__ void decompose(const Geo& g, int c, int& i, int& j, int& k)
 {
-    unsigned uc = (unsigned)c;
-    unsigned t = uc / (unsigned)g.nx;
-    i = (int)(uc - t * (unsigned)g.nx);
-    unsigned kk = t / (unsigned)g.ny;
-    j = (int)(t - kk * (unsigned)g.ny);
-    k = (int)kk;
+    const int row = g.dx.div(c);
+    i = c - row * g.nx;
+    k = g.dy.div(row);
+    j = row - k * g.ny;
 }
 
 template <typename T> struct Fields { T* f[NF]; };
@@ -180,36 +212,6 @@ __device__ __forceinline__ Par<T> parabola_finish(T qmm, T qm, T q0, T qp, T qpp
     p.dq = fR - fL;
     p.q6 = T(6) * (q0 - T(0.5) * (fL + fR));
     return p;
-}
-
-// Steps 1-5 for the cell with line values qmm, qm, q0, qp, qpp
-template <typename T>
-__device__ __forceinline__ Par<T> parabola(T qmm, T qm, T q0, T qp, T qpp)
-{
-    T dm_m = limited_slope(qmm, qm, q0);
-    T dm_0 = limited_slope(qm, q0, qp);
-    T dm_p = limited_slope(q0, qp, qpp);
-    T qL = interface_value(qm, q0, dm_m, dm_0);
-    T qR = interface_value(q0, qp, dm_0, dm_p);
-    return parabola_finish(qmm, qm, q0, qp, qpp, qL, qR, dm_0);
-}
-
-// parabolas of the two cells on either side of a face from the 6-cell line
-// q0..q5 (cells i-3..i+2; left cell i-1, right cell i): the middle slopes and
-// the face value q_{i-1/2} are shared, so this is the same arithmetic as two
-// separate calls
-template <typename T>
-__device__ __forceinline__ void parabola_pair(T q0, T q1, T q2, T q3, T q4, T q5, Par<T>& PL, Par<T>& PR)
-{
-    T d1 = limited_slope(q0, q1, q2);
-    T d2 = limited_slope(q1, q2, q3);
-    T d3 = limited_slope(q2, q3, q4);
-    T d4 = limited_slope(q3, q4, q5);
-    T f12 = interface_value(q1, q2, d1, d2);
-    T f23 = interface_value(q2, q3, d2, d3);
-    T f34 = interface_value(q3, q4, d3, d4);
-    PL = parabola_finish(q0, q1, q2, q3, q4, f12, f23, d2);
-    PR = parabola_finish(q1, q2, q3, q4, q5, f23, f34, d3);
 }
 
 // Sec. 2.4: average over the right part of relative width y (the q(-nu t) formula)

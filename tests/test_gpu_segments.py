@@ -1,6 +1,6 @@
 """Boxes at the edges of the launch tilings: sides around the segment lengths
 and wavefronts of the marching kernels, sides of one to three cells, and rows
-around the block widths.  FP64 against the oracle at the bound of
+around the block widths and in pieces.  FP64 against the oracle at the bound of
 tolerance.py, after two steps at the oracle's CFL step."""
 import pytest
 
@@ -22,7 +22,10 @@ def _need_gpu():
 
 # (nz, ny, nx)
 SHAPES = [(1, 1, 200), (2, 3, 5), (1, 33, 64), (33, 1, 63), (31, 65, 17), (65, 32, 33), (97, 5, 130), (7, 67, 65),
-          (3, 40, 257)]
+          (3, 40, 257),
+          # rows in pieces with halos: two and more per row, even and ragged,
+          # several pieces and parts of rows in a block
+          (2, 3, 252), (3, 2, 301), (2, 5, 515), (5, 1, 767), (2, 2, 1031)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
