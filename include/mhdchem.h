@@ -146,7 +146,9 @@ int mhd_init_state(mhd_box *b, const double *prim);
 int mhd_set_state(mhd_box *b, const double *cons);
 
 /* Copy the current conserved state to host FP64 (MHD_NFIELDS fields).  Synchronises;
- * returns a latched fault if any. */
+ * returns a latched fault if any.  Large states pass through pinned slots of
+ * the box (up to 32 MiB, kept until mhd_destroy) to pageable memory, copied
+ * by up to eight threads that end with the call. */
 int mhd_get_state(mhd_box *b, double *cons_out);
 
 /* Gravitational potential of the current density (Sec. 2.9: the Poisson

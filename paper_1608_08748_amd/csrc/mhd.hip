@@ -21,13 +21,16 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
 #include <deque>
+#include <memory>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -43,6 +46,18 @@ using namespace mhd;
 // launches whose event pairs the timing ring holds (a step makes at most a
 // few dozen)
 constexpr int EVCAP = 1024;
+
+// Pinned slots through which states leave for the caller's pageable memory
+// (copy_out), allocated at the first use and released with their owner: an
+// eighth of the state each, at most 4 MiB.
+constexpr int RING_SLOTS = 8;
+constexpr size_t RING_SLOT_MAX = (size_t)4 << 20;
+struct HostRing {
+    char* mem = nullptr;        // RING_SLOTS slots, then the fault flags
+    size_t slot = 0;            // bytes per slot
+    hipEvent_t ev[RING_SLOTS];
+    int nev = 0;
+};
 
 struct mhd_box {
     mhd_params p;
@@ -74,6 +89,7 @@ struct mhd_box {
     int ev_ready;
     double tms[MHD_NKCLASS];
     int64_t tcnt[MHD_NKCLASS];
+    HostRing ring;
 };
 
 namespace {
@@ -835,13 +851,200 @@ int full_step(mhd_box* b, double dt, bool dev)
     return b->nev >= EVCAP / 2 ? timing_collect(b) : MHD_OK;
 }
 
+int flags_status(uint32_t fl)
+{
+    if (fl & 1u) return MHD_ENONPHYS;
+    if (fl & 2u) return MHD_ECFL;
+    return MHD_OK;
+}
+
 int sync_and_flags(mhd_box* b)
 {
     uint32_t fl = 0;
     if (hipMemcpyAsync(&fl, b->flags, sizeof(fl), hipMemcpyDeviceToHost, b->s) != hipSuccess) return MHD_EDEVICE;
     if (hipStreamSynchronize(b->s) != hipSuccess) return MHD_EDEVICE;
-    if (fl & 1u) return MHD_ENONPHYS;
-    if (fl & 2u) return MHD_ECFL;
+    return flags_status(fl);
+}
+
+// ---------------------------------------------------------------- host copies
+
+// threads that copy `bytes` of host memory beside the caller's (0: too little
+// to be worth starting one): fresh pages of the caller's are
+// zeroed by the kernel as they are first written, at about 20 GB/s per thread
+// with large pages and a fifth of that without
+int copy_threads(size_t bytes)
+{
+    const size_t most = std::min<size_t>(8, std::max(1u, std::thread::hardware_concurrency()));
+    const size_t n = std::min<size_t>(most, bytes / ((size_t)2 << 20));
+    return n > 1 ? (int)n : 0;
+}
+
+// Runs work(t, nt) on nt threads beside the caller's own lead(nt), nt at most
+// `threads` (fewer where the system gives no more; none: lead(0) does the work).
+template <class Lead, class Work>
+int with_threads(int threads, Lead&& lead, Work&& work)
+{
+    std::vector<std::thread> pool;
+    std::atomic<int> go{ -1 };
+    try {
+        pool.reserve(threads);
+        for (int t = 0; t < threads; t++)
+            pool.emplace_back([&, t] {
+                int nt;
+                while ((nt = go.load(std::memory_order_acquire)) < 0) std::this_thread::yield();
+                work(t, nt);
+            });
+    } catch (...) {   // no further thread: go on with those there are
+    }
+    const int nt = (int)pool.size();
+    go.store(nt, std::memory_order_release);
+    const int st = lead(nt);
+    for (std::thread& t : pool) t.join();
+    return st;
+}
+
+// memcpy of host memory by several threads
+void host_copy(void* dst, const void* src, size_t bytes)
+{
+    auto part = [&](int t, int nt) {
+        const size_t a = bytes / nt * t, e = t + 1 == nt ? bytes : bytes / nt * (t + 1);
+        memcpy(static_cast<char*>(dst) + a, static_cast<const char*>(src) + a, e - a);
+    };
+    with_threads(copy_threads(bytes),
+                 [&](int nt) {
+                     if (nt == 0) part(0, 1);
+                     return MHD_OK;
+                 },
+                 part);
+}
+
+bool ring_ready(HostRing& r, size_t bytes)
+{
+    const size_t want = std::min(RING_SLOT_MAX, align256((bytes + RING_SLOTS - 1) / RING_SLOTS));
+    if (r.mem && r.slot < want) {   // a server's ring, sized for a smaller box
+        (void)hipHostFree(r.mem);
+        r.mem = nullptr;
+    }
+    if (!r.mem) {
+        if (hipHostMalloc(reinterpret_cast<void**>(&r.mem), RING_SLOTS * want + 256, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            r.mem = nullptr;
+            return false;
+        }
+        r.slot = want;
+    }
+    while (r.nev < RING_SLOTS) {
+        if (hipEventCreateWithFlags(&r.ev[r.nev], hipEventDisableTiming) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        r.nev++;
+    }
+    return true;
+}
+
+void ring_release(HostRing& r)
+{
+    for (int i = 0; i < r.nev; i++) (void)hipEventDestroy(r.ev[i]);
+    if (r.mem) (void)hipHostFree(r.mem);
+    r.mem = nullptr;
+    r.nev = 0;
+}
+
+// Device ranges of values to consecutive FP64 values of pageable host memory,
+// and the fault flags.  The values pass through the ring's pinned slots in the
+// order of the ranges: this thread keeps the copies to the slots queued and
+// announces each that has arrived, the others copy (and widen) its slices to
+// the caller's memory.  Before the first one arrives, while steps still run,
+// they write a byte to every page of their slices, so that the pages are there.
+// (Straight into fresh pageable memory the runtime copies at 10 GB/s; a 256^3
+// FP64 state, 1.48 GB, takes 150 ms that way.  FP32 values cross the link as
+// they are and are widened here, exactly.)
+struct Range {
+    const void* dev;
+    size_t n;
+};
+
+template <typename T>
+int copy_out(hipStream_t s, HostRing& ring, const Range* ranges, int nranges, double* host, const uint32_t* flags_dev,
+             uint32_t* flags)
+{
+    const size_t most = ring.slot / sizeof(T);   // values per chunk
+    struct Chunk {
+        const T* dev;
+        double* dst;
+        size_t n;
+    };
+    std::vector<Chunk> ch;
+    size_t total = 0;
+    for (int r = 0; r < nranges; r++) {
+        for (size_t o = 0; o < ranges[r].n; o += most)
+            ch.push_back({ static_cast<const T*>(ranges[r].dev) + o, host + total + o,
+                           std::min(most, ranges[r].n - o) });
+        total += ranges[r].n;
+    }
+    const int nch = (int)ch.size();
+    std::atomic<int> arrived{ 0 };            // chunks in the slots (past nch: give up)
+    std::atomic<int> taken[RING_SLOTS] = {};  // slices copied out of each slot
+    uint32_t* fl = reinterpret_cast<uint32_t*>(ring.mem + RING_SLOTS * ring.slot);
+    auto slot = [&](int k) { return reinterpret_cast<T*>(ring.mem + (size_t)(k % RING_SLOTS) * ring.slot); };
+    auto take = [&](int k, int t, int nt) {
+        const Chunk& c = ch[k];
+        const size_t a = c.n / nt * t, e = t + 1 == nt ? c.n : c.n / nt * (t + 1);
+        const T* src = slot(k);
+        if constexpr (sizeof(T) == sizeof(double)) {
+            memcpy(c.dst + a, src + a, (e - a) * sizeof(double));
+        } else {
+            for (size_t i = a; i < e; i++) c.dst[i] = (double)src[i];
+        }
+    };
+    auto work = [&](int t, int nt) {
+        for (int k = 0; k < nch && arrived.load(std::memory_order_relaxed) == 0; k++) {
+            const size_t a = ch[k].n / nt * t, e = t + 1 == nt ? ch[k].n : ch[k].n / nt * (t + 1);
+            for (size_t i = a; i < e; i += 4096 / sizeof(double)) *(volatile char*)(ch[k].dst + i) = 0;
+        }
+        for (int k = 0; k < nch; k++) {
+            int n;
+            for (int spin = 0; (n = arrived.load(std::memory_order_acquire)) <= k; spin++) {
+                if (spin < 1000) std::this_thread::yield();
+                else std::this_thread::sleep_for(std::chrono::microseconds(20));
+            }
+            if (n > nch) return;
+            take(k, t, nt);
+            taken[k % RING_SLOTS].fetch_add(1, std::memory_order_release);
+        }
+    };
+    // a slot is filled again LAG chunks after the announcement of the chunk it
+    // held, so that a slow thread does not hold up the next announcement
+    constexpr int LAG = 2;
+    auto lead = [&](int nt) {
+        int st = MHD_OK;
+        auto issue = [&](int k) {
+            if (k >= RING_SLOTS && nt > 0)
+                while (taken[k % RING_SLOTS].load(std::memory_order_acquire) < nt * (k / RING_SLOTS))
+                    std::this_thread::yield();
+            if (hipMemcpyAsync(slot(k), ch[k].dev, ch[k].n * sizeof(T), hipMemcpyDeviceToHost, s) != hipSuccess ||
+                hipEventRecord(ring.ev[k % RING_SLOTS], s) != hipSuccess)
+                st = MHD_EDEVICE;
+        };
+        if (hipMemcpyAsync(fl, flags_dev, sizeof(uint32_t), hipMemcpyDeviceToHost, s) != hipSuccess) st = MHD_EDEVICE;
+        int issued = 0;
+        for (; st == MHD_OK && issued < nch && issued < RING_SLOTS - LAG; issued++) issue(issued);
+        for (int k = 0; st == MHD_OK && k < nch; k++) {
+            if (hipEventSynchronize(ring.ev[k % RING_SLOTS]) != hipSuccess) {
+                st = MHD_EDEVICE;
+                break;
+            }
+            if (nt == 0) take(k, 0, 1);
+            arrived.store(k + 1, std::memory_order_release);
+            if (issued < nch) issue(issued++);
+        }
+        if (st != MHD_OK) arrived.store(nch + 1, std::memory_order_release);
+        return st;
+    };
+    const int st = with_threads(copy_threads(total * sizeof(double)), lead, work);
+    if (st != MHD_OK) return st;
+    *flags = *fl;
     return MHD_OK;
 }
 
@@ -888,20 +1091,50 @@ int load_f64(mhd_box* b, const double* host, bool prim, bool wait = true)
     return MHD_OK;
 }
 
-template <typename T>
-int get_f64(mhd_box* b, double* host)
+// whether the runtime holds this host memory pinned (it then copies to it at
+// the rate of the link)
+bool pinned(const void* host)
 {
-    size_t N = (size_t)b->g.n;
-    double* stage = reinterpret_cast<double*>(b->F[0]);
-    typename BToF64<T>::Args ta;
-    ta.g = b->g;
-    ta.U = cview(view<T>(b, b->cur[GH], b->cur[GM], b->cur[GB]));
-    ta.dst = stage;
-    k_one<BToF64<T>><<<b->nblocks, NTH, 0, b->s>>>(ta);
-    if (launch_status()) return MHD_EDEVICE;
-    if (hipMemcpyAsync(host, stage, NF * N * sizeof(double), hipMemcpyDeviceToHost, b->s) != hipSuccess)
-        return MHD_EDEVICE;
-    return sync_and_flags(b);
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, host) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeHost;
+}
+
+// states below this many FP64 bytes leave in one copy of the runtime's (32^3,
+// 2.9 MB: 0.21 ms, through the ring 0.23 ms and 1 ms more at its first use)
+constexpr size_t RING_MIN = (size_t)8 << 20;
+
+// the current state to host FP64 (the groups H, M, B in host field order)
+template <typename T>
+int get_f64(mhd_box* b, HostRing& ring, double* host)
+{
+    const size_t N = (size_t)b->g.n;
+    const Fields<T> u = view<T>(b, b->cur[GH], b->cur[GM], b->cur[GB]);
+    if (NF * N * sizeof(double) < RING_MIN || pinned(host) || !ring_ready(ring, NF * N * sizeof(T))) {
+        typename BToF64<T>::Args ta;
+        ta.g = b->g;
+        ta.U = cview(u);
+        ta.dst = reinterpret_cast<double*>(b->F[0]);
+        k_one<BToF64<T>><<<b->nblocks, NTH, 0, b->s>>>(ta);
+        if (launch_status()) return MHD_EDEVICE;
+        if (hipMemcpyAsync(host, ta.dst, NF * N * sizeof(double), hipMemcpyDeviceToHost, b->s) != hipSuccess)
+            return MHD_EDEVICE;
+        return sync_and_flags(b);
+    }
+    static_assert(RHO == 0 && MX == 1 && EI == 5 && BX == 6 && BZ == 8 && H2 == 9 && HP == 10 && NF == 11,
+                  "groups of the host field order");
+    const Range r[5] = { { u.f[RHO], N }, { u.f[MX], 5 * N }, { u.f[BX], 3 * N }, { u.f[H2], N }, { u.f[HP], N } };
+    uint32_t fl = 0;
+    int st;
+    try {
+        st = copy_out<T>(b->s, ring, r, 5, host, b->flags, &fl);
+    } catch (const std::bad_alloc&) {
+        return MHD_ENOMEM;
+    }
+    return st ? st : flags_status(fl);
 }
 
 template <typename T>
@@ -969,6 +1202,18 @@ double now_s()
 
 // ---------------------------------------------------------------- server
 
+// FP64 values of a request or a result in host memory, not initialised
+struct HostState {
+    std::unique_ptr<double[]> v;
+    size_t n = 0;
+    bool resize(size_t count)
+    {
+        v.reset(new (std::nothrow) double[count]);
+        n = v ? count : 0;
+        return n == count;
+    }
+};
+
 struct mhd_server {
     mhd_server_params p;
     hipStream_t s;
@@ -981,7 +1226,7 @@ struct mhd_server {
     struct Pending {
         uint64_t id;
         mhd_request r;
-        std::vector<double> prim;       // copied state, or
+        HostState prim;                 // copied state, or
         const double* src = nullptr;    // the caller's state, borrowed
         double t_submit;
     };
@@ -995,7 +1240,8 @@ struct mhd_server {
     std::deque<Pending> pending;
     std::vector<Active> active;
     std::deque<mhd_completion> done;
-    std::unordered_map<uint64_t, std::vector<double>> results;
+    std::unordered_map<uint64_t, HostState> results;
+    HostRing ring;
     uint64_t next_id;
     double t0;
     std::vector<MultiRec> recs;
@@ -1098,7 +1344,7 @@ int server_admit(mhd_server* sv)
         box_bind(b, &bp, L);
         // a copied state is freed below, so its upload completes first; a
         // borrowed one stays valid until the completion is polled
-        const double* src = q.src ? q.src : q.prim.data();
+        const double* src = q.src ? q.src : q.prim.v.get();
         const bool wait = q.src == nullptr;
         int st = sv->p.precision == MHD_FP64 ? load_f64<double>(b, src, true, wait)
                                              : load_f64<float>(b, src, true, wait);
@@ -1204,11 +1450,12 @@ int server_retire(mhd_server* sv, mhd_server::Retiring& r, int half)
     c.status = s2;
     if (a.keep) {
         // the kept state is copied out before the box's memory is released
-        std::vector<double> buf((size_t)NF * a.box->g.n);
-        int s3 = sv->p.precision == MHD_FP64 ? get_f64<double>(a.box, buf.data())
-                                             : get_f64<float>(a.box, buf.data());
-        if (s3 == MHD_OK || s3 == s2) sv->results[a.id].swap(buf);
-        else if (s3 == MHD_EDEVICE) return s3;
+        HostState buf;
+        if (!buf.resize((size_t)NF * a.box->g.n)) return MHD_ENOMEM;
+        int s3 = sv->p.precision == MHD_FP64 ? get_f64<double>(a.box, sv->ring, buf.v.get())
+                                             : get_f64<float>(a.box, sv->ring, buf.v.get());
+        if (s3 == MHD_OK || s3 == s2) std::swap(sv->results[a.id], buf);
+        else if (s3 == MHD_EDEVICE || s3 == MHD_ENOMEM) return s3;
         pool_free(sv, a.off, a.bytes);
     }
     c.t_done = now_s() - sv->t0;
@@ -1394,7 +1641,7 @@ int mhd_set_state(mhd_box* b, const double* cons)
 int mhd_get_state(mhd_box* b, double* cons_out)
 {
     if (!b || !cons_out) return MHD_EINVAL;
-    return b->prec == MHD_FP64 ? get_f64<double>(b, cons_out) : get_f64<float>(b, cons_out);
+    return b->prec == MHD_FP64 ? get_f64<double>(b, b->ring, cons_out) : get_f64<float>(b, b->ring, cons_out);
 }
 
 int mhd_get_potential(mhd_box* b, double* phi_out)
@@ -1471,6 +1718,7 @@ int mhd_destroy(mhd_box* b)
 {
     if (b && b->ev_ready)
         for (int i = 0; i < 2 * EVCAP; i++) (void)hipEventDestroy(b->ev[i]);
+    if (b) ring_release(b->ring);
     delete b;
     return MHD_OK;
 }
@@ -1560,7 +1808,10 @@ int mhd_server_submit(mhd_server* sv, const mhd_request* r, const double* prim, 
     if (r->borrow)
         q.src = prim;
     else
-        q.prim.assign(prim, prim + (size_t)MHD_NPRIM * n);
+    {
+        if (!q.prim.resize((size_t)MHD_NPRIM * n)) return MHD_ENOMEM;
+        host_copy(q.prim.v.get(), prim, q.prim.n * sizeof(double));
+    }
     q.t_submit = now_s() - sv->t0;
     sv->pending.push_back(std::move(q));
     *id = sv->pending.back().id;
@@ -1590,8 +1841,8 @@ int mhd_server_result(mhd_server* sv, uint64_t id, double* cons_out, size_t coun
     if (!sv || !cons_out) return MHD_EINVAL;
     auto it = sv->results.find(id);
     if (it == sv->results.end()) return MHD_EINVAL;
-    if (count != it->second.size()) return MHD_EINVAL;
-    memcpy(cons_out, it->second.data(), count * sizeof(double));
+    if (count != it->second.n) return MHD_EINVAL;
+    host_copy(cons_out, it->second.v.get(), count * sizeof(double));
     sv->results.erase(it);
     return MHD_OK;
 }
@@ -1616,6 +1867,7 @@ int mhd_server_destroy(mhd_server* sv)
         (void)hipEventDestroy(sv->ev[1]);
     }
     if (sv->htab) (void)hipHostFree(sv->htab);
+    ring_release(sv->ring);
     delete sv;
     return MHD_OK;
 }
