@@ -184,7 +184,7 @@ int mhd_conserved_totals(mhd_box *b, double out[MHD_NFIELDS]);
  * hipMalloc): the FP64 totals of mhd_conserved_totals (same kernels, same
  * fixed-order tree, so the same bits for the same stored values) of a state
  * held in the caller's own device memory.  Allocates nothing: the per-block
- * partial sums live in a static device array of the library (5.5 MiB per
+ * partial sums live in a static device array of the library (44 KiB per
  * device, held until the process ends).
  *   state      device pointer: MHD_NFIELDS fields of n[0]*n[1]*n[2] values,
  *              field order and layout of the box state (structure of arrays,

@@ -153,6 +153,12 @@ size_t face_values(bool ion) { return ion ? NFACE + 1 : NFACE; }
 
 void march_segments(mhd_box* b, double share);
 
+// chunks of the totals' partial sums: of 4096 cells (16 per thread), and at
+// most 512, one wave's eight loads per lane in the last sum
+constexpr int TOTALS_CELLS = 4096, TOTALS_CHUNKS = 512;
+int totals_per_chunk(int n) { return std::max(TOTALS_CELLS, (n - 1) / TOTALS_CHUNKS + 1); }
+int totals_chunks(int n) { return (n - 1) / totals_per_chunk(n) + 1; }
+
 Layout layout_of(const int32_t n[3], int precision, bool grav, bool ion)
 {
     Layout L;
@@ -164,9 +170,9 @@ Layout layout_of(const int32_t n[3], int precision, bool grav, bool ion)
     // the face scratch doubles as host staging (MHD_NPRIM or NF FP64 fields)
     size_t stage = align256((size_t)NF * N * 8);
     L.F = 3 * fbytes > stage ? 3 * fbytes : stage;
-    // per-block partials: the totals (NF per cell-parallel block); the CFL
-    // speed maxima need one
-    L.part = align256(nb * NF * sizeof(double));
+    // partials: the CFL speed maxima (one per cell-parallel block) and the
+    // totals (NF per chunk)
+    L.part = align256(std::max(nb, (size_t)NF * totals_chunks((int)N)) * sizeof(double));
     L.misc = 3 * 256;
     // self-gravity: the potential and the FFT tables (the complex scratch of
     // the Poisson solve is the x face scratch, free at that point)
@@ -1138,19 +1144,27 @@ int get_f64(mhd_box* b, HostRing& ring, double* host)
 }
 
 template <typename T>
-int totals_launch(mhd_box* b)
+int totals_run(const CFields<T>& u, int n, hipStream_t s, double* part, double* out)
 {
     typename BTotalsPartial<T>::Args pa;
-    pa.g = b->g;
-    pa.U = cview(view<T>(b, b->cur[GH], b->cur[GM], b->cur[GB]));
-    pa.part = b->part;
-    k_one<BTotalsPartial<T>><<<b->nblocks, NTH, 0, b->s>>>(pa);
+    pa.n = n;
+    pa.per = totals_per_chunk(n);
+    pa.chunks = totals_chunks(n);
+    pa.U = u;
+    pa.part = part;
+    k_one<BTotalsPartial<T>><<<NF * pa.chunks, NTH, 0, s>>>(pa);
     BTotalsFinal::Args fa;
-    fa.part = b->part;
-    fa.nparts = b->nblocks;
-    fa.out = b->tot_dev;
-    k_one<BTotalsFinal><<<1, BTotalsFinal::NT, 0, b->s>>>(fa);
+    fa.part = part;
+    fa.chunks = pa.chunks;
+    fa.out = out;
+    k_one<BTotalsFinal><<<1, BTotalsFinal::NT, 0, s>>>(fa);
     return launch_status();
+}
+
+template <typename T>
+int totals_launch(mhd_box* b)
+{
+    return totals_run<T>(cview(view<T>(b, b->cur[GH], b->cur[GM], b->cur[GB])), b->g.n, b->s, b->part, b->tot_dev);
 }
 
 template <typename T>
@@ -1523,14 +1537,12 @@ int server_progress(mhd_server* sv, int* nact, int* npend)
 
 // ---------------------------------------------------------------- allocation-free totals
 
-// Per-block partial sums of mhd_conserved_totals_noalloc: NF doubles for each
-// 256-cell block of a box of at most MHD_NOALLOC_MAX_CELLS cells (5.5 MiB).
+// Partial sums of mhd_conserved_totals_noalloc: NF doubles per chunk (44 KiB).
 // Each device that loads the library holds its own copy until the process
 // ends.  Host code never passes the array's name to a kernel (on the host it
 // is a stand-in, not a device address): it uses the address that
 // hipGetSymbolAddress returned for the current device.
-constexpr size_t NOALLOC_BLOCKS = ((size_t)MHD_NOALLOC_MAX_CELLS + NTH - 1) / NTH;
-static __device__ __align__(256) double scratch[NOALLOC_BLOCKS * NF];
+static __device__ __align__(256) double scratch[(size_t)TOTALS_CHUNKS * NF];
 
 namespace {
 
@@ -1555,21 +1567,11 @@ int scratch_of_current_device(double** out)
 }
 
 template <typename T>
-int totals_noalloc(const void* state, const Geo& g, hipStream_t s, double* part, double* out)
+int totals_noalloc(const void* state, int n, hipStream_t s, double* part, double* out)
 {
-    typename BTotalsPartial<T>::Args pa;
-    pa.g = g;
-    const T* base = static_cast<const T*>(state);
-    for (int f = 0; f < NF; f++) pa.U.f[f] = base + (size_t)f * (size_t)g.n;
-    pa.part = part;
-    const int nblocks = (g.n + NTH - 1) / NTH;
-    k_one<BTotalsPartial<T>><<<nblocks, NTH, 0, s>>>(pa);
-    BTotalsFinal::Args fa;
-    fa.part = part;
-    fa.nparts = nblocks;
-    fa.out = out;
-    k_one<BTotalsFinal><<<1, BTotalsFinal::NT, 0, s>>>(fa);
-    return launch_status();
+    CFields<T> u;
+    for (int f = 0; f < NF; f++) u.f[f] = static_cast<const T*>(state) + (size_t)f * (size_t)n;
+    return totals_run<T>(u, n, s, part, out);
 }
 
 }  // namespace
@@ -1700,10 +1702,9 @@ int mhd_conserved_totals_noalloc(const void* state, int32_t precision, const int
     double* part = nullptr;
     int st = scratch_of_current_device(&part);
     if (st) return st;
-    const Geo g = make_geo(n[0], n[1], n[2]);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    return precision == MHD_FP64 ? totals_noalloc<double>(state, g, s, part, out)
-                                 : totals_noalloc<float>(state, g, s, part, out);
+    return precision == MHD_FP64 ? totals_noalloc<double>(state, (int)cells, s, part, out)
+                                 : totals_noalloc<float>(state, (int)cells, s, part, out);
 }
 
 int mhd_debug_stage(mhd_box* b, int stage, double dt)

@@ -1636,60 +1636,66 @@ struct BReduceDt {
     }
 };
 
-// FP64 totals: per-block fixed-order sums of the NF fields
+// FP64 totals in a fixed order: block (chunk, field) sums `per` consecutive
+// cells of one field, each thread eight running sums over every 256th cell, so
+// that eight loads are in flight per thread and the sums carry few terms;
+// then one wave per field sums the chunks.  Bound by the read of the state: at
+// 256^3 FP64 (1.48 GB) the pass takes 238 us, 6.2 TB/s.  (One block per 256
+// cells of all fields left 65536 x 11 partial sums to a single last block:
+// 978 us in all.)
 template <typename T>
 struct BTotalsPartial {
     static constexpr int NT = NTH;
     static constexpr bool XCD = false;
+    static constexpr int ACC = 8;
     struct Args {
-        Geo g;
+        int n, per, chunks;
         CFields<T> U;
-        double* part;
+        double* part;   // NF x chunks
     };
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
     {
-        __shared__ double red[NF][NTH / 64];
-        int c = blk * NT + tid;
-        int lane = tid & 63, wv = tid >> 6;
+        __shared__ double red[NTH / 64];
+        const int f = blk / A.chunks, ck = blk - f * A.chunks;
+        const T* u = A.U.f[f];
+        const int c1 = min(A.n - ck * A.per, A.per);   // cells of this chunk
+        u += (size_t)ck * A.per;
+        double s[ACC] = {};
+        int c = tid;
+        for (; c + (ACC - 1) * NT < c1; c += ACC * NT) {
+            T v[ACC];
 #pragma unroll
-        for (int f = 0; f < NF; f++) {
-            double v = c < A.g.n ? (double)A.U.f[f][c] : 0.0;
-            v = wave_sum(v);
-            if (lane == 0) red[f][wv] = v;
+            for (int k = 0; k < ACC; k++) v[k] = u[c + k * NT];
+#pragma unroll
+            for (int k = 0; k < ACC; k++) s[k] += (double)v[k];
         }
+#pragma unroll
+        for (int k = 0; k < ACC; k++)
+            if (c + k * NT < c1) s[k] += (double)u[c + k * NT];
+        const double v = wave_sum(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])));
+        if ((tid & 63) == 0) red[tid >> 6] = v;
         __syncthreads();
-        if (tid < NF) {
-            double s = 0.0;
-            for (int w = 0; w < NTH / 64; w++) s += red[tid][w];
-            A.part[(size_t)blk * NF + tid] = s;
-        }
+        if (tid == 0) A.part[blk] = (red[0] + red[1]) + (red[2] + red[3]);
     }
 };
 
 struct BTotalsFinal {
-    static constexpr int NT = 1024;
+    static constexpr int NT = 64 * NF;
     static constexpr bool XCD = false;
     struct Args {
         const double* part;
-        int nparts;
+        int chunks;
         double* out;
     };
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
     {
-        __shared__ double red[NF][16];
-        int lane = tid & 63, wv = tid >> 6;
-        for (int f = 0; f < NF; f++) {
-            double s = 0.0;
-            for (int t = tid; t < A.nparts; t += NT) s += A.part[(size_t)t * NF + f];
-            s = wave_sum(s);
-            if (lane == 0) red[f][wv] = s;
-        }
-        __syncthreads();
-        if (tid < NF) {
-            double s = 0.0;
-            for (int w = 0; w < 16; w++) s += red[tid][w];
-            A.out[tid] = s;
-        }
+        const int f = tid >> 6, lane = tid & 63;
+        const double* p = A.part + (size_t)f * A.chunks;
+        double s = 0.0;
+#pragma unroll 8
+        for (int t = lane; t < A.chunks; t += 64) s += p[t];
+        s = wave_sum(s);
+        if (lane == 0) A.out[f] = s;
     }
 };
 
