@@ -234,8 +234,9 @@ enum {
  * mhd_get_timing waits for all of them. */
 int mhd_set_timing(mhd_box *b, int enable);
 
-/* Accumulated device time (ms) and launch count per kernel class since
- * timing was enabled.  ms and counts have MHD_NKCLASS entries. */
+/* Accumulated device time (ms) and kernel count per kernel class since timing
+ * was enabled (a launch that holds two directions or two field groups counts
+ * both).  ms and counts have MHD_NKCLASS entries. */
 int mhd_get_timing(mhd_box *b, double *ms, int64_t *counts);
 
 /* Release the box (not the workspace, not the stream). */

@@ -85,7 +85,7 @@ struct mhd_box {
     int timing;
     int nev;
     hipEvent_t ev[2 * EVCAP];
-    int evcls[EVCAP];
+    int evcls[EVCAP], evparts[EVCAP];
     int ev_ready;
     double tms[MHD_NKCLASS];
     int64_t tcnt[MHD_NKCLASS];
@@ -292,15 +292,17 @@ struct Slots { int h, m, b; };
 
 // ---------------------------------------------------------------- emitters
 
-// event pair around one launch of class cls (no-op unless timing is on)
+// event pair around one launch of class cls that holds `parts` of the step's
+// kernels (no-op unless timing is on)
 struct KTimer {
     mhd_box* b;
     int slot;
-    KTimer(mhd_box* box, int cls) : b(box), slot(-1)
+    KTimer(mhd_box* box, int cls, int parts) : b(box), slot(-1)
     {
         if (b && b->timing && b->nev < EVCAP) {
             slot = b->nev++;
             b->evcls[slot] = cls;
+            b->evparts[slot] = parts;
             (void)hipEventRecord(b->ev[2 * slot], b->s);
         }
     }
@@ -318,7 +320,7 @@ int timing_collect(mhd_box* b)
         float ms = 0.f;
         if (hipEventElapsedTime(&ms, b->ev[2 * i], b->ev[2 * i + 1]) != hipSuccess) return MHD_EDEVICE;
         b->tms[b->evcls[i]] += ms;
-        b->tcnt[b->evcls[i]] += 1;
+        b->tcnt[b->evcls[i]] += b->evparts[i];
     }
     b->nev = 0;
     return MHD_OK;
@@ -328,10 +330,10 @@ int timing_collect(mhd_box* b)
 struct OneEmit {
     mhd_box* b;
     template <class Body>
-    void launch(int cls, int blocks, size_t shm, const typename Body::Args& a)
+    void launch(int cls, int blocks, size_t shm, const typename Body::Args& a, int parts = 1)
     {
         if (blocks <= 0) return;
-        KTimer t(b, cls);
+        KTimer t(b, cls, parts);
         if (shm > 65536)
             (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_one<Body>),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
@@ -410,7 +412,7 @@ struct MultiEmit {
     bool first;      // the first box defines the program
     bool mismatch;
     template <class Body>
-    void launch(int, int blocks, size_t shm, const typename Body::Args& a)
+    void launch(int, int blocks, size_t shm, const typename Body::Args& a, int = 1)
     {
         if (first) {
             MultiRec r;
@@ -537,18 +539,19 @@ void march_segments(mhd_box* b, double share)
     const Geo& g = b->g;
     const bool d = b->esz == 8;
     auto waves = [&](double threads) { return share * threads / 64.0; };
-    // NONADV faces: two (FP64) or three waves per SIMD
+    // NONADV faces: two (FP64) or three waves per SIMD; both directions in one
+    // launch
     const int occ = d ? 2 : 3;
     const double more = d ? 0.65 : 0.4;
-    b->seg_fy = best_segment(g.ny, waves((double)g.nx * g.nz), SIMD, occ, more, d ? 1.5 : 2.5);
-    b->seg_fz = best_segment(g.nz, waves((double)g.nx * g.ny), SIMD, occ, more, d ? 1.5 : 2.5);
+    b->seg_fy = best_segment(g.ny, 2.0 * waves((double)g.nx * g.nz), SIMD, occ, more, d ? 1.5 : 2.5);
+    b->seg_fz = best_segment(g.nz, 2.0 * waves((double)g.nx * g.ny), SIMD, occ, more, d ? 1.5 : 2.5);
     b->seg_ay = best_segment(g.ny, waves((double)g.nx * g.nz), SIMD, d ? 2 : 4, d ? 0.65 : 0.35, 2.5);
     // fused ADV update: three (FP64) or four blocks of 256 threads per CU, two
-    // of 512
+    // of 512; both field groups in one launch (but for FP64 with the network)
     const bool wide = wide_rows(g, b->esz);
     const RowTile rt = row_tile(g.nx, wide ? 512 : ROW_NT);
     const double groups = std::ceil((double)g.ny * rt.spr / rt.rpb);
-    b->seg_xz = best_segment(g.nz, share * groups, CU, wide ? 2 : (d ? 3 : 4), d ? 0.6 : 0.5, 1.0);
+    b->seg_xz = best_segment(g.nz, (d && b->p.ionisation ? 1.0 : 2.0) * share * groups, CU, wide ? 2 : (d ? 3 : 4), d ? 0.6 : 0.5, 1.0);
     b->seg_b = best_segment(g.nz, waves((double)g.nx * g.ny), SIMD, 4, 0.25, 0.7);
 }
 
@@ -581,22 +584,18 @@ void emit_nonadv_substage_t(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout
     fa.dbg = dbg;
     fa.phi = phi;
     // y and z faces: marching segments
-    for (int D = 1; D <= 2; D++) {
-        const int nd = D == 1 ? g.ny : g.nz;
-        const int no = D == 1 ? g.nz : g.ny;
-        fa.seg = D == 1 ? b->seg_fy : b->seg_fz;
-        fa.F = D == 1 ? F1 : F2;
-        long long threads = (long long)g.nx * no * ((nd + fa.seg - 1) / fa.seg);
-        int blocks = (int)((threads + NTH - 1) / NTH);
-        if (D == 1)
-            e.template launch<BFaceMarch<T, 1, ION>>(MHD_K_NONADV_FACE, blocks, 0, fa);
-        else
-            e.template launch<BFaceMarch<T, 2, ION>>(MHD_K_NONADV_FACE, blocks, 0, fa);
-    }
+    auto march_blocks = [&](int nd, int no, int seg) {
+        const long long threads = (long long)g.nx * no * ((nd + seg - 1) / seg);
+        return (int)((threads + NTH - 1) / NTH);
+    };
+    fa.seg_y = b->seg_fy;
+    fa.seg_z = b->seg_fz;
+    fa.nby = march_blocks(g.ny, g.nz, fa.seg_y);
+    e.template launch<BFaceMarch<T, ION>>(MHD_K_NONADV_FACE, fa.nby + march_blocks(g.nz, g.ny, fa.seg_z), 0, fa,
+                                           2);
     // x faces; the launch of the first substage checks an explicit dt
     // against the last device CFL bound
     fa.F = F0;
-    fa.seg = 0;
     fa.dt_cfl = first ? b->dt_dev : nullptr;
     const bool wide = wide_rows(g, sizeof(T));
     fa.rt = row_tile(g.nx, wide ? 512 : ROW_NT);
@@ -647,15 +646,21 @@ void emit_adv_face(mhd_box* b, Emit& e, const Fields<T>& in, const StepArgs& a)
     e.template launch<BAdvFaceMarchY<T, NQ>>(MHD_K_ADV_FACE, (int)((threads + NTH - 1) / NTH), 0, ma);
 }
 
-// the two field-group launches of the fused ADV update with blocks of NT
-// threads (dynamic LDS: 2 x (NV + 2 NQ) x NT values)
+// the fused ADV update with blocks of NT threads, one launch for both field
+// groups where their registers allow (dynamic LDS: 2 x (NV + 2 NQ) x NT values)
 template <typename T, int NT, class Emit>
-void emit_adv_xz(Emit& e, const AdvXZArgs<T>& xa, int blocks, bool ion)
+void emit_adv_xz(Emit& e, const AdvXZArgs<T>& xa, bool ion)
 {
     auto shm = [](int nv, int nq) { return (size_t)2 * (nv + 2 * nq) * NT * sizeof(T); };
-    e.template launch<BAdvXZUpdate<T, 0, 4, NT>>(MHD_K_ADV_UPDATE, blocks, shm(4, 4), xa);   // rho, m
-    if (ion) e.template launch<BAdvXZUpdate<T, 4, 4, NT>>(MHD_K_ADV_UPDATE, blocks, shm(6, 4), xa);
-    else e.template launch<BAdvXZUpdate<T, 4, 3, NT>>(MHD_K_ADV_UPDATE, blocks, shm(5, 3), xa);
+    const int both = (xa.tiles + 7) / 8 * 16;
+    if (!ion) {
+        e.template launch<BAdvXZPair<T, 3, NT>>(MHD_K_ADV_UPDATE, both, shm(4, 4), xa, 2);
+    } else if constexpr (sizeof(T) == 4) {
+        e.template launch<BAdvXZPair<T, 4, NT>>(MHD_K_ADV_UPDATE, both, shm(6, 4), xa, 2);
+    } else {
+        e.template launch<BAdvXZUpdate<T, 0, 4, NT>>(MHD_K_ADV_UPDATE, xa.tiles, shm(4, 4), xa);   // rho, m
+        e.template launch<BAdvXZUpdate<T, 4, 4, NT>>(MHD_K_ADV_UPDATE, xa.tiles, shm(6, 4), xa);   // E, e, h2, hp
+    }
 }
 
 // One ADV substage: y faces marched along y, then the update with its x and z
@@ -682,11 +687,11 @@ void emit_adv_substage(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout, con
     xa.rt = row_tile(b->g.nx, wide ? 512 : ROW_NT);
     xa.nrg = (int)(((long long)b->g.ny * xa.rt.spr + xa.rt.rpb - 1) / xa.rt.rpb);
     xa.seg = b->seg_xz;
-    const int blocks = xa.nrg * ((b->g.nz + xa.seg - 1) / xa.seg);
+    xa.tiles = xa.nrg * ((b->g.nz + xa.seg - 1) / xa.seg);
     if constexpr (sizeof(T) == 4) {
-        if (wide) emit_adv_xz<T, 512>(e, xa, blocks, ion);
+        if (wide) emit_adv_xz<T, 512>(e, xa, ion);
     }
-    if (!wide) emit_adv_xz<T, ROW_NT>(e, xa, blocks, ion);
+    if (!wide) emit_adv_xz<T, ROW_NT>(e, xa, ion);
 }
 
 // NONADV stage: the M and B groups each rotate through their three slots

@@ -277,10 +277,11 @@ template <typename T>
 struct FaceArgs {
     Geo g;
     CFields<T> U;            // substage input state
-    T* F;
+    T* F;                    // x-face outputs (row kernel)
     StepArgs a;
     RowTile rt;              // row segments (row kernel)
-    int seg;                 // faces per thread (marching kernel)
+    int seg_y, seg_z;        // faces per thread (marching kernel)
+    int nby;                 // y-march blocks
     uint32_t* flags;
     const double* dt_cfl;    // non-null: check the explicit dt against this CFL bound
     // the x-row kernel also updates m, E, e (the NONADV update of Sec. 2.2,
@@ -288,8 +289,8 @@ struct FaceArgs {
     // z face outputs, and the gravitational potential (null without gravity)
     CFields<T> S;
     Fields<T> O;
-    const T* Fy;
-    const T* Fz;
+    T* Fy;
+    T* Fz;
     RK rk;
     int dbg;                 // 1: write tau R(U) instead of the combination
     const T* phi;
@@ -561,16 +562,28 @@ struct BFaceXRows {
 // segment (seg + 1 per seg faces); threads are consecutive in x, so every load
 // is coalesced.  With per-cell differences the thread also solves the upper
 // face of its segment's last cell; the previous face's fluxes wait in LDS.
-template <typename T, int D, bool ION>
+// Both directions share a launch, the y blocks first: the two are independent,
+// so a small box pays the latency of one march instead of two, and a large one
+// has one ragged end instead of two.
+template <typename T, bool ION>
 struct BFaceMarch {
     static constexpr int NT = NTH;
     static constexpr bool XCD = false;
+    // two waves per SIMD (FP64 needs 254-258 registers unbounded)
+    static constexpr int MINW = sizeof(T) == 8 ? 2 : 1;
     using Args = FaceArgs<T>;
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
     {
+        if (blk < A.nby) march<1>(A, blk, tid);
+        else march<2>(A, blk - A.nby, tid);
+    }
+    template <int D>
+    static __device__ __forceinline__ void march(const Args& A, int blk, int tid)
+    {
         const Geo& g = A.g;
         const size_t N = (size_t)g.n;
-        const int seg = A.seg;
+        const int seg = D == 1 ? A.seg_y : A.seg_z;
+        T* const F = D == 1 ? A.Fy : A.Fz;
         const int nd = D == 1 ? g.ny : g.nz;
         const int no = D == 1 ? g.nz : g.ny;
         const int nseg = (nd + seg - 1) / seg;
@@ -686,16 +699,16 @@ struct BFaceMarch {
                        R, gm, ION ? gw[1] : gm, ION ? gw[2] : gm, ION, ydx, srl, srr, out);
             srl = srr;
             if (!DIFF) {
-                store_face(A.F, N, c, out);
+                store_face(F, N, c, out);
             } else {
                 if (x < x1) {
-                    A.F[5 * N + c] = out[5];
-                    A.F[6 * N + c] = out[6];
+                    F[5 * N + c] = out[5];
+                    F[6 * N + c] = out[6];
                 }
                 if (x > x0) {
                     const int cm = base + (x - 1) * stride;
 #pragma unroll
-                    for (int v = 0; v < 5; v++) A.F[v * N + cm] = out[v] - prev[v][tid];
+                    for (int v = 0; v < 5; v++) F[v * N + cm] = out[v] - prev[v][tid];
                 }
 #pragma unroll
                 for (int v = 0; v < 5; v++) prev[v][tid] = out[v];
@@ -1294,6 +1307,7 @@ struct AdvXZArgs {
     int dbg;
     RowTile rt; // segments of a plane's rows
     int nrg;    // groups of rpb segments: ceil(ny * spr / rpb)
+    int tiles;  // nrg times the z segments
     int seg;    // z cells per block
 };
 
@@ -1551,6 +1565,29 @@ struct BAdvXZUpdate {
             }
         }
         for (; x < x1; x++) plane(x);
+    }
+};
+
+// Both field groups in one launch, eight tiles of the first group and the same
+// eight of the second in turn, so that a tile's two blocks run on one XCD (block
+// b on XCD b % 8) at about the same time and share their rho and momenta in its
+// L2; a small box pays the latency of one march instead of two.  (FP64 with the
+// H+ field keeps two launches: the second group's registers leave two waves per
+// SIMD, the first group alone three.)
+template <typename T, int NQ2, int MAXT>
+struct BAdvXZPair {
+    using G1 = BAdvXZUpdate<T, 0, 4, MAXT>;
+    using G2 = BAdvXZUpdate<T, 4, NQ2, MAXT>;
+    static constexpr int NT = MAXT;
+    static constexpr bool XCD = false;
+    static constexpr int MINW = G1::MINW;
+    using Args = AdvXZArgs<T>;
+    static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
+    {
+        const int tile = (blk >> 4) * 8 + (blk & 7);
+        if (tile >= A.tiles) return;   // the whole block: before any barrier
+        if (blk & 8) G2::run(A, tile, tid);
+        else G1::run(A, tile, tid);
     }
 };
 
