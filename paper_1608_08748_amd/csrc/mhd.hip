@@ -263,11 +263,12 @@ int launch_status() { return hipGetLastError() == hipSuccess ? MHD_OK : MHD_EDEV
 StepArgs step_args(mhd_box* b, double dt, bool dev)
 {
     StepArgs a;
-    a.dt_val = dt;
-    a.dt_dev = dev ? b->dt_dev : nullptr;
     a.gamma = b->p.gamma;
     a.h = 1.0 / (double)b->p.n[0];
-    a.theta = b->p.theta;
+    a.dt_val[DT] = dt;
+    a.dt_val[DTDX] = dt / a.h;
+    a.dt_val[YDX] = b->p.theta * (dt / a.h);
+    a.dt_dev = dev ? b->dt_dev : nullptr;
     // the bound is computed from the stored state: FP32 storage moves it by ~1e-7
     a.cfl_tol = b->prec == MHD_FP64 ? 1e-12 : 1e-4;
     a.ion = b->p.ionisation;
@@ -326,8 +327,15 @@ int timing_collect(mhd_box* b)
     return MHD_OK;
 }
 
-// sends each launch of the program straight to the box's stream
+// whether a field of the box is longer than the kernels' 32-bit byte offsets
+// reach (more than 2^29 cells in FP64, 2^30 in FP32)
+bool wide_fields(const mhd_box* b) { return (uint64_t)b->g.n * b->esz > ((uint64_t)1 << 32); }
+
+// sends each launch of the program straight to the box's stream; O: the type of
+// the kernels' byte offsets
+template <typename O>
 struct OneEmit {
+    using Off = O;
     mhd_box* b;
     template <class Body>
     void launch(int cls, int blocks, size_t shm, const typename Body::Args& a, int parts = 1)
@@ -406,7 +414,9 @@ int go_persist(const void* tab, const int* bstart, int nbox, int blocks, size_t 
     }
 }
 
+template <typename O>
 struct MultiEmit {
+    using Off = O;
     std::vector<MultiRec>* recs;
     size_t k;        // program position within the current box
     bool first;      // the first box defines the program
@@ -562,6 +572,7 @@ template <typename T, bool ION, class Emit>
 void emit_nonadv_substage_t(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout, const StepArgs& a, RK rk,
                             int dbg, bool first)
 {
+    using O = typename Emit::Off;
     Fields<T> in = view<T>(b, sin.h, sin.m, sin.b);
     Fields<T> S = view<T>(b, sS.h, sS.m, sS.b);
     Fields<T> out = view<T>(b, sout.h, sout.m, sout.b);
@@ -591,7 +602,7 @@ void emit_nonadv_substage_t(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout
     fa.seg_y = b->seg_fy;
     fa.seg_z = b->seg_fz;
     fa.nby = march_blocks(g.ny, g.nz, fa.seg_y);
-    e.template launch<BFaceMarch<T, ION>>(MHD_K_NONADV_FACE, fa.nby + march_blocks(g.nz, g.ny, fa.seg_z), 0, fa,
+    e.template launch<BFaceMarch<T, ION, O>>(MHD_K_NONADV_FACE, fa.nby + march_blocks(g.nz, g.ny, fa.seg_z), 0, fa,
                                            2);
     // x faces; the launch of the first substage checks an explicit dt
     // against the last device CFL bound
@@ -602,10 +613,10 @@ void emit_nonadv_substage_t(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout
     const int xblocks = (int)(((long long)g.ny * g.nz * fa.rt.spr + fa.rt.rpb - 1) / fa.rt.rpb);
     if constexpr (sizeof(T) == 4) {
         if (wide)
-            e.template launch<BFaceXRows<T, 512, ION>>(MHD_K_NONADV_FACE, xblocks, 512 * XROW_SLOTS * sizeof(T), fa);
+            e.template launch<BFaceXRows<T, 512, ION, O>>(MHD_K_NONADV_FACE, xblocks, 512 * XROW_SLOTS * sizeof(T), fa);
     }
     if (!wide)
-        e.template launch<BFaceXRows<T, ROW_NT, ION>>(MHD_K_NONADV_FACE, xblocks, ROW_NT * XROW_SLOTS * sizeof(T), fa);
+        e.template launch<BFaceXRows<T, ROW_NT, ION, O>>(MHD_K_NONADV_FACE, xblocks, ROW_NT * XROW_SLOTS * sizeof(T), fa);
     FieldUpdateArgs<T> ua;
     ua.g = g;
     ua.U = cview(in);
@@ -619,7 +630,7 @@ void emit_nonadv_substage_t(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout
     ua.dbg = dbg;
     ua.zt = ztile_of(g, UPD_NT, UPD_TX);
     ua.zt.seg = b->seg_b;
-    e.template launch<BFieldUpdate<T>>(MHD_K_NONADV_UPDATE, ztile_blocks(g, ua.zt), 0, ua);
+    e.template launch<BFieldUpdate<T, O>>(MHD_K_NONADV_UPDATE, ztile_blocks(g, ua.zt), 0, ua);
 }
 
 template <typename T, class Emit>
@@ -636,14 +647,15 @@ void emit_nonadv_substage(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout, 
 template <typename T, int NQ, class Emit>
 void emit_adv_face(mhd_box* b, Emit& e, const Fields<T>& in, const StepArgs& a)
 {
-    typename BAdvFaceMarchY<T, NQ>::Args ma;
+    using O = typename Emit::Off;
+    typename BAdvFaceMarchY<T, NQ, O>::Args ma;
     ma.g = b->g;
     ma.U = cview(in);
     ma.a = a;
     ma.F = reinterpret_cast<T*>(b->F[1]);
     ma.seg = b->seg_ay;
     long long threads = (long long)b->g.nx * b->g.nz * ((b->g.ny + ma.seg - 1) / ma.seg);
-    e.template launch<BAdvFaceMarchY<T, NQ>>(MHD_K_ADV_FACE, (int)((threads + NTH - 1) / NTH), 0, ma);
+    e.template launch<BAdvFaceMarchY<T, NQ, O>>(MHD_K_ADV_FACE, (int)((threads + NTH - 1) / NTH), 0, ma);
 }
 
 // the fused ADV update with blocks of NT threads, one launch for both field
@@ -651,15 +663,16 @@ void emit_adv_face(mhd_box* b, Emit& e, const Fields<T>& in, const StepArgs& a)
 template <typename T, int NT, class Emit>
 void emit_adv_xz(Emit& e, const AdvXZArgs<T>& xa, bool ion)
 {
+    using O = typename Emit::Off;
     auto shm = [](int nv, int nq) { return (size_t)2 * (nv + 2 * nq) * NT * sizeof(T); };
     const int both = (xa.tiles + 7) / 8 * 16;
     if (!ion) {
-        e.template launch<BAdvXZPair<T, 3, NT>>(MHD_K_ADV_UPDATE, both, shm(4, 4), xa, 2);
+        e.template launch<BAdvXZPair<T, 3, NT, O>>(MHD_K_ADV_UPDATE, both, shm(4, 4), xa, 2);
     } else if constexpr (sizeof(T) == 4) {
-        e.template launch<BAdvXZPair<T, 4, NT>>(MHD_K_ADV_UPDATE, both, shm(6, 4), xa, 2);
+        e.template launch<BAdvXZPair<T, 4, NT, O>>(MHD_K_ADV_UPDATE, both, shm(6, 4), xa, 2);
     } else {
-        e.template launch<BAdvXZUpdate<T, 0, 4, NT>>(MHD_K_ADV_UPDATE, xa.tiles, shm(4, 4), xa);   // rho, m
-        e.template launch<BAdvXZUpdate<T, 4, 4, NT>>(MHD_K_ADV_UPDATE, xa.tiles, shm(6, 4), xa);   // E, e, h2, hp
+        e.template launch<BAdvXZUpdate<T, 0, 4, NT, O>>(MHD_K_ADV_UPDATE, xa.tiles, shm(4, 4), xa);   // rho, m
+        e.template launch<BAdvXZUpdate<T, 4, 4, NT, O>>(MHD_K_ADV_UPDATE, xa.tiles, shm(6, 4), xa);   // E, e, h2, hp
     }
 }
 
@@ -733,6 +746,8 @@ void emit_reduce_dt(mhd_box* b, Emit& e, int nparts)
     ra.part = b->part;
     ra.nparts = nparts;
     ra.cflh = b->p.cfl * (1.0 / (double)b->p.n[0]);
+    ra.h = 1.0 / (double)b->p.n[0];
+    ra.theta = b->p.theta;
     ra.dt = b->dt_dev;
     e.template launch<BReduceDt>(MHD_K_REDUCE, 1, 0, ra);
 }
@@ -740,7 +755,8 @@ void emit_reduce_dt(mhd_box* b, Emit& e, int nparts)
 template <typename T, class Emit>
 void emit_tail(mhd_box* b, Emit& e, const StepArgs& a, int mode)
 {
-    typename BTail<T>::Args ta;
+    using O = typename Emit::Off;
+    typename BTail<T, O>::Args ta;
     ta.g = b->g;
     ta.U = view<T>(b, b->cur[GH], b->cur[GM], b->cur[GB]);
     ta.a = a;
@@ -748,7 +764,7 @@ void emit_tail(mhd_box* b, Emit& e, const StepArgs& a, int mode)
     ta.mode = mode;
     ta.part = b->part;
     ta.flags = b->flags;
-    e.template launch<BTail<T>>(MHD_K_TAIL, b->nblocks, 0, ta);
+    e.template launch<BTail<T, O>>(MHD_K_TAIL, b->nblocks, 0, ta);
     emit_reduce_dt(b, e, b->nblocks);
 }
 
@@ -849,12 +865,24 @@ void emit_step(mhd_box* b, Emit& e, const StepArgs& a)
 
 // ---------------------------------------------------------------- single-box operations
 
+// f(e) with the box's emitter
+template <class F>
+void with_emit(mhd_box* b, F&& f)
+{
+    if (wide_fields(b)) {
+        OneEmit<uint64_t> e{ b };
+        f(e);
+    } else {
+        OneEmit<uint32_t> e{ b };
+        f(e);
+    }
+}
+
 template <typename T>
 int full_step(mhd_box* b, double dt, bool dev)
 {
     StepArgs a = step_args(b, dt, dev);
-    OneEmit e{ b };
-    emit_step<T>(b, e, a);
+    with_emit(b, [&](auto& e) { emit_step<T>(b, e, a); });
     int st = launch_status();
     if (st) return st;
     // the event ring is read (a wait on its last event) only once half of it
@@ -1074,27 +1102,28 @@ int load_f64(mhd_box* b, const double* host, bool prim, bool wait = true)
     Fields<T> u = view<T>(b, 0, 0, 0);
     int saved = b->timing;
     b->timing = 0;
-    OneEmit e{ b };
-    if (prim) {
-        typename BInit<T>::Args ia;
-        ia.g = b->g;
-        ia.Wp = stage;
-        ia.U = u;
-        ia.gamma = b->p.gamma;
-        ia.ion = b->p.ionisation;
-        e.template launch<BInit<T>>(MHD_K_SETUP, b->nblocks, 0, ia);
-    } else {
-        typename BFromF64<T>::Args ia;
-        ia.g = b->g;
-        ia.src = stage;
-        ia.U = u;
-        e.template launch<BFromF64<T>>(MHD_K_SETUP, b->nblocks, 0, ia);
-    }
-    BClearFlags::Args ca;
-    ca.flags = b->flags;
-    e.template launch<BClearFlags>(0, 1, 0, ca);
-    StepArgs a = step_args(b, 0.0, false);
-    emit_tail<T>(b, e, a, 0);
+    with_emit(b, [&](auto& e) {
+        if (prim) {
+            typename BInit<T>::Args ia;
+            ia.g = b->g;
+            ia.Wp = stage;
+            ia.U = u;
+            ia.gamma = b->p.gamma;
+            ia.ion = b->p.ionisation;
+            e.template launch<BInit<T>>(MHD_K_SETUP, b->nblocks, 0, ia);
+        } else {
+            typename BFromF64<T>::Args ia;
+            ia.g = b->g;
+            ia.src = stage;
+            ia.U = u;
+            e.template launch<BFromF64<T>>(MHD_K_SETUP, b->nblocks, 0, ia);
+        }
+        BClearFlags::Args ca;
+        ca.flags = b->flags;
+        e.template launch<BClearFlags>(0, 1, 0, ca);
+        StepArgs a = step_args(b, 0.0, false);
+        emit_tail<T>(b, e, a, 0);
+    });
     b->timing = saved;
     int st = launch_status();
     if (st) return st;
@@ -1185,30 +1214,35 @@ template <typename T>
 int debug_stage(mhd_box* b, int stage, double dt)
 {
     StepArgs a = step_args(b, dt, false);
-    OneEmit e{ b };
-    if (b->grav && (stage == MHD_STAGE_NONADV || stage == MHD_STAGE_NONADV_RHS)) emit_poisson<T>(b, e);
-    switch (stage) {
-    case MHD_STAGE_NONADV: emit_nonadv_stage<T>(b, e, a, false); break;
-    case MHD_STAGE_ADV: emit_adv_stage<T>(b, e, a); break;
-    case MHD_STAGE_TAIL: emit_tail<T>(b, e, a, 1); break;
-    case MHD_STAGE_NONADV_RHS:
-    case MHD_STAGE_ADV_RHS: {
-        // tau R(U) of one substage into all ten fields of a free slot; needs
-        // the three groups in one slot (true right after mhd_set_state)
-        int S = b->cur[GM];
-        if (b->cur[GH] != S || b->cur[GB] != S) return MHD_EINVAL;
-        int O = (S + 1) % 3;
-        Slots s0 = { S, S, S }, so = { O, O, O };
-        if (stage == MHD_STAGE_NONADV_RHS)
-            emit_nonadv_substage<T>(b, e, s0, s0, so, a, rk_coef[0], 1, false);
-        else
-            emit_adv_substage<T>(b, e, s0, s0, so, a, rk_coef[0], 1);
-        b->cur[GH] = b->cur[GM] = b->cur[GB] = O;
-        break;
-    }
-    default: return MHD_EINVAL;
-    }
-    return launch_status();
+    int st = MHD_OK;
+    with_emit(b, [&](auto& e) {
+        if (b->grav && (stage == MHD_STAGE_NONADV || stage == MHD_STAGE_NONADV_RHS)) emit_poisson<T>(b, e);
+        switch (stage) {
+        case MHD_STAGE_NONADV: emit_nonadv_stage<T>(b, e, a, false); break;
+        case MHD_STAGE_ADV: emit_adv_stage<T>(b, e, a); break;
+        case MHD_STAGE_TAIL: emit_tail<T>(b, e, a, 1); break;
+        case MHD_STAGE_NONADV_RHS:
+        case MHD_STAGE_ADV_RHS: {
+            // tau R(U) of one substage into all ten fields of a free slot; needs
+            // the three groups in one slot (true right after mhd_set_state)
+            int S = b->cur[GM];
+            if (b->cur[GH] != S || b->cur[GB] != S) {
+                st = MHD_EINVAL;
+                return;
+            }
+            int O = (S + 1) % 3;
+            Slots s0 = { S, S, S }, so = { O, O, O };
+            if (stage == MHD_STAGE_NONADV_RHS)
+                emit_nonadv_substage<T>(b, e, s0, s0, so, a, rk_coef[0], 1, false);
+            else
+                emit_adv_substage<T>(b, e, s0, s0, so, a, rk_coef[0], 1);
+            b->cur[GH] = b->cur[GM] = b->cur[GB] = O;
+            break;
+        }
+        default: st = MHD_EINVAL;
+        }
+    });
+    return st ? st : launch_status();
 }
 
 double now_s()
@@ -1389,11 +1423,11 @@ int server_admit(mhd_server* sv)
 }
 
 // one step of every active box, merged into one launch per program position
-template <typename T>
+template <typename T, typename O>
 int server_step(mhd_server* sv, int half)
 {
     sv->recs.clear();
-    MultiEmit e{ &sv->recs, 0, true, false };
+    MultiEmit<O> e{ &sv->recs, 0, true, false };
     double cells = 0.0;
     for (const mhd_server::Active& a : sv->active) cells += (double)a.box->g.n;
     for (size_t i = 0; i < sv->active.size(); i++) {
@@ -1491,7 +1525,12 @@ int server_progress(mhd_server* sv, int* nact, int* npend)
     const int half = (int)(sv->rounds & 1);
     bool launched = false;
     if (!sv->active.empty()) {
-        st = sv->p.precision == MHD_FP64 ? server_step<double>(sv, half) : server_step<float>(sv, half);
+        bool wide = false;
+        for (const mhd_server::Active& a : sv->active) wide = wide || wide_fields(a.box);
+        if (sv->p.precision == MHD_FP64)
+            st = wide ? server_step<double, uint64_t>(sv, half) : server_step<double, uint32_t>(sv, half);
+        else
+            st = wide ? server_step<float, uint64_t>(sv, half) : server_step<float, uint32_t>(sv, half);
         if (st) return st;
         // boxes that have run their steps leave the round: their totals and
         // flags go to pinned slots behind the round on the stream, and (unless
@@ -1654,7 +1693,7 @@ int mhd_get_state(mhd_box* b, double* cons_out)
 int mhd_get_potential(mhd_box* b, double* phi_out)
 {
     if (!b || !phi_out || !b->grav) return MHD_EINVAL;
-    OneEmit e{ b };
+    OneEmit<uint32_t> e{ b };   // the Poisson kernels index by cell
     const size_t N = (size_t)b->g.n;
     if (b->prec == MHD_FP64) {
         emit_poisson<double>(b, e);

@@ -11,19 +11,28 @@
 
 namespace mhd {
 
+// what the kernels take from the step's dt: dt itself, dt / h and the width
+// theta dt / h of the parabola averages
+enum { DT = 0, DTDX, YDX, NDT };
+
 struct StepArgs {
-    double dt_val;          // explicit step, or
-    const double* dt_dev;   // device-resident CFL step when non-null
+    double dt_val[NDT];     // explicit step, or
+    const double* dt_dev;   // the same of the device-resident CFL step when non-null
     double gamma;
     double h;               // 1 / nx
-    double theta;
     double cfl_tol;         // relative slack of the dt <= CFL-bound check
     int ion;                // ionisation network: per-cell gamma_eff (primitive slot 8)
 };
 
-__device__ __forceinline__ double step_dt(const StepArgs& a)
+// The values come formed (by the dt reduction or the host): an FP64 quotient
+// takes a thread about 20 instructions, and the x-row kernel has one cell per
+// thread.  They do not change while a kernel runs, so they are read as
+// constants, on the scalar unit, and take no vector register.
+template <int I>
+__device__ __forceinline__ double step_val(const StepArgs& a)
 {
-    return a.dt_dev ? *a.dt_dev : a.dt_val;
+    using Const = const __attribute__((address_space(4))) double*;
+    return a.dt_dev ? ((Const)a.dt_dev)[I] : a.dt_val[I];
 }
 
 struct RK { double a, b; };
@@ -224,22 +233,22 @@ __global__ __launch_bounds__(Body::NT) __attribute__((amdgpu_waves_per_eu(MinWav
 // and, with the ionisation network, the H2 and H+ densities
 template <typename T> struct Raw { T rho, mn, m1, m2, e, b1, b1p, b2, b2p, h2, hp; };
 
-template <typename T, int D, bool ION>
+template <typename T, int D, bool ION, typename O>
 __device__ __forceinline__ void raw_load(const CFields<T>& U, int c, int c1, int c2, Raw<T>& r)
 {
     constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
-    r.rho = U.f[RHO][c];
-    r.mn = U.f[MX + D][c];
-    r.m1 = U.f[MX + T1][c];
-    r.m2 = U.f[MX + T2][c];
-    r.e = U.f[EI][c];
-    r.b1 = U.f[BX + T1][c];
-    r.b1p = U.f[BX + T1][c1];
-    r.b2 = U.f[BX + T2][c];
-    r.b2p = U.f[BX + T2][c2];
+    r.rho = at<O>(U.f[RHO], c);
+    r.mn = at<O>(U.f[MX + D], c);
+    r.m1 = at<O>(U.f[MX + T1], c);
+    r.m2 = at<O>(U.f[MX + T2], c);
+    r.e = at<O>(U.f[EI], c);
+    r.b1 = at<O>(U.f[BX + T1], c);
+    r.b1p = at<O>(U.f[BX + T1], c1);
+    r.b2 = at<O>(U.f[BX + T2], c);
+    r.b2p = at<O>(U.f[BX + T2], c2);
     if (ION) {
-        r.h2 = U.f[H2][c];
-        r.hp = U.f[HP][c];
+        r.h2 = at<O>(U.f[H2], c);
+        r.hp = at<O>(U.f[HP], c);
     }
 }
 
@@ -266,11 +275,11 @@ __device__ __forceinline__ void raw_prim(const Raw<T>& r, double gamma, T q[6], 
 
 // ---------------------------------------------------------------- NONADV faces
 
-template <typename T>
+template <typename O, typename T>
 __device__ __forceinline__ void store_face(T* __restrict__ F, size_t N, int c, const T out[7])
 {
 #pragma unroll
-    for (int q = 0; q < 7; q++) F[q * N + c] = out[q];
+    for (int q = 0; q < 7; q++) at<O>(F + q * N, c) = out[q];
 }
 
 template <typename T>
@@ -301,7 +310,7 @@ struct FaceArgs {
 template <typename T>
 __device__ __forceinline__ void check_dt(const FaceArgs<T>& A, int blk, int tid)
 {
-    if (blk == 0 && tid == 0 && A.dt_cfl && !A.a.dt_dev && A.a.dt_val > *A.dt_cfl * (1.0 + A.a.cfl_tol))
+    if (blk == 0 && tid == 0 && A.dt_cfl && !A.a.dt_dev && A.a.dt_val[DT] > *A.dt_cfl * (1.0 + A.a.cfl_tol))
         atomicOr(A.flags, 2u);
 }
 
@@ -330,7 +339,7 @@ template <typename T> struct FluxDiff { static constexpr bool v = sizeof(T) == 4
 // needs one barrier.
 constexpr int XROW_SLOTS = 18;
 
-template <typename T, int MAXT, bool ION>
+template <typename T, int MAXT, bool ION, typename O>
 struct BFaceXRows {
     static constexpr int NT = MAXT;
     static constexpr bool XCD = false;
@@ -369,11 +378,6 @@ struct BFaceXRows {
         // periodic offsets of the upper neighbours along y and z
         const int dyp = ((j + 1 == g.ny ? 0 : j + 1) - j) * nx;
         const int dzp = ((k + 1 == g.nz ? 0 : k + 1) - k) * g.nxy;
-        // the step's dt (device-resident under the CFL step), read before any
-        // store of this kernel: read later, each wave would wait for the load
-        // after a barrier, with every other wave of the block
-        const double dt_now = step_dt(A.a);
-
         // own cell: conserved values, primitives
         // uc, sc: the cell's m, E, e at the substage input and at the stage
         // start, for the update at the end.  With EARLY they are taken here
@@ -386,16 +390,16 @@ struct BFaceXRows {
         const int upd[5] = { MX, MY, MZ, EN, EI };
         if (rc.live) {
             Raw<T> rw;
-            raw_load<T, 0, ION>(A.U, c, c + dyp, c + dzp, rw);
-            bn = A.U.f[BX][c];
+            raw_load<T, 0, ION, O>(A.U, c, c + dyp, c + dzp, rw);
+            bn = at<O>(A.U.f[BX], c);
             if constexpr (EARLY) {
                 uc[0] = rw.mn;
                 uc[1] = rw.m1;
                 uc[2] = rw.m2;
-                uc[3] = A.U.f[EN][c];
+                uc[3] = at<O>(A.U.f[EN], c);
                 uc[4] = rw.e;
 #pragma unroll
-                for (int q = 0; q < 5; q++) sc[q] = A.S.f[upd[q]][c];
+                for (int q = 0; q < 5; q++) sc[q] = at<O>(A.S.f[upd[q]], c);
             }
             raw_prim<T, ION>(rw, A.a.gamma, q2, gam);
             rho = rw.rho;
@@ -471,26 +475,26 @@ struct BFaceXRows {
             }
             // parabola variables 3, 4, 5 are Bt1, Bt2, p
             face_solve(rl, q1[5], q1[3], q1[4], rho, q2[5], q2[3], q2[4], bn, L, R, gm, gl, gam, ION,
-                       T(A.a.theta * (dt_now / A.a.h)), srl, srho, out);
+                       T(step_val<YDX>(A.a)), srl, srho, out);
             if (rc.own) {
 #pragma unroll
                 for (int v = 0; v < 5; v++) {
-                    fy[v] = A.Fy[v * N + c];
-                    fz[v] = A.Fz[v * N + c];
+                    fy[v] = at<O>(A.Fy + v * N, c);
+                    fz[v] = at<O>(A.Fz + v * N, c);
                     if constexpr (!DIFF) {
-                        fyp[v] = A.Fy[v * N + c + dyp];
-                        fzp[v] = A.Fz[v * N + c + dzp];
+                        fyp[v] = at<O>(A.Fy + v * N, c + dyp);
+                        fzp[v] = at<O>(A.Fz + v * N, c + dzp);
                     }
                 }
                 if constexpr (!EARLY) {
 #pragma unroll
                     for (int q = 0; q < 5; q++) {
-                        uc[q] = A.U.f[upd[q]][c];
-                        sc[q] = A.S.f[upd[q]][c];
+                        uc[q] = at<O>(A.U.f[upd[q]], c);
+                        sc[q] = at<O>(A.S.f[upd[q]], c);
                     }
                 }
-                A.F[5 * N + c] = out[5];
-                A.F[6 * N + c] = out[6];
+                at<O>(A.F + 5 * N, c) = out[5];
+                at<O>(A.F + 6 * N, c) = out[6];
             }
 #pragma unroll
             for (int v = 0; v < 5; v++) sm[(8 + v) * NT + tid] = out[v];
@@ -500,7 +504,7 @@ struct BFaceXRows {
 
         // update of m, E, e: flux differences of the x faces (the right
         // cell's lower face from LDS), y and z faces (loaded above)
-        const T dtdx = T(dt_now / A.a.h);
+        const T dtdx = T(step_val<DTDX>(A.a));
         T dF[3][5];
 #pragma unroll
         for (int v = 0; v < 5; v++) {
@@ -528,12 +532,12 @@ struct BFaceXRows {
             // m and -m . grad(Phi) on E, central differences
             const T* ph = A.phi;
             const T i2h = T(0.5 / A.a.h);
-            const T dt = T(dt_now);
+            const T dt = T(step_val<DT>(A.a));
             const int dxp = (rc.i + 1 == nx ? 0 : rc.i + 1) - rc.i, dxm = (rc.i == 0 ? nx - 1 : rc.i - 1) - rc.i;
             const int dym = ((j == 0 ? g.ny - 1 : j - 1) - j) * nx;
             const int dzm = ((k == 0 ? g.nz - 1 : k - 1) - k) * g.nxy;
-            T gv[3] = { (ph[c + dxp] - ph[c + dxm]) * i2h, (ph[c + dyp] - ph[c + dym]) * i2h,
-                        (ph[c + dzp] - ph[c + dzm]) * i2h };
+            T gv[3] = { (at<O>(ph, c + dxp) - at<O>(ph, c + dxm)) * i2h, (at<O>(ph, c + dyp) - at<O>(ph, c + dym)) * i2h,
+                        (at<O>(ph, c + dzp) - at<O>(ph, c + dzm)) * i2h };
             T work = T(0);
 #pragma unroll
             for (int a = 0; a < 3; a++) {
@@ -544,14 +548,14 @@ struct BFaceXRows {
         }
         if (A.dbg) {
 #pragma unroll
-            for (int q = 0; q < 5; q++) A.O.f[upd[q]][c] = inc[q];
-            A.O.f[RHO][c] = T(0);
-            A.O.f[H2][c] = T(0);
-            if (ION) A.O.f[HP][c] = T(0);   // H+ is a field of its own only with the network
+            for (int q = 0; q < 5; q++) at<O>(A.O.f[upd[q]], c) = inc[q];
+            at<O>(A.O.f[RHO], c) = T(0);
+            at<O>(A.O.f[H2], c) = T(0);
+            if (ION) at<O>(A.O.f[HP], c) = T(0);   // H+ is a field of its own only with the network
         } else {
             const T ra = T(A.rk.a), rb = T(A.rk.b);
 #pragma unroll
-            for (int q = 0; q < 5; q++) A.O.f[upd[q]][c] = (uc[q] + ra * (sc[q] - uc[q])) + rb * inc[q];
+            for (int q = 0; q < 5; q++) at<O>(A.O.f[upd[q]], c) = (uc[q] + ra * (sc[q] - uc[q])) + rb * inc[q];
         }
     }
 };
@@ -565,7 +569,7 @@ struct BFaceXRows {
 // Both directions share a launch, the y blocks first: the two are independent,
 // so a small box pays the latency of one march instead of two, and a large one
 // has one ragged end instead of two.
-template <typename T, bool ION>
+template <typename T, bool ION, typename O>
 struct BFaceMarch {
     static constexpr int NT = NTH;
     static constexpr bool XCD = false;
@@ -596,7 +600,7 @@ struct BFaceMarch {
         const int x0 = sgi * seg;
         const int x1 = min(x0 + seg, nd);
         const T gm = T(A.a.gamma);
-        const T ydx = T(A.a.theta * (step_dt(A.a) / A.a.h));
+        const T ydx = T(step_val<YDX>(A.a));
         // offsets of the upper neighbours along t1, t2 (the same for every
         // cell of the line): y march t1 = z, t2 = x; z march t1 = x, t2 = y
         const int dxp = (i + 1 == g.nx ? 0 : i + 1) - i;
@@ -611,7 +615,7 @@ struct BFaceMarch {
         for (int m = 0; m < 5; m++) {
             int cc = base + wrapc(x0 - 3 + m, nd) * stride;
             Raw<T> rw;
-            raw_load<T, D, ION>(A.U, cc, cc + o1, cc + o2, rw);
+            raw_load<T, D, ION, O>(A.U, cc, cc + o1, cc + o2, rw);
             T qm[6];
             raw_prim<T, ION>(rw, A.a.gamma, qm, gw[m]);
 #pragma unroll
@@ -643,7 +647,7 @@ struct BFaceMarch {
         Raw<T> nr;
         auto fetch = [&](int x) {
             int cn = base + wrapc(x + 2, nd) * stride;
-            raw_load<T, D, ION>(A.U, cn, cn + o1, cn + o2, nr);
+            raw_load<T, D, ION, O>(A.U, cn, cn + o1, cn + o2, nr);
         };
         constexpr bool DIFF = FluxDiff<T>::v;
         const int xe = DIFF ? x1 + 1 : x1;   // faces solved: x0 .. xe - 1
@@ -656,7 +660,7 @@ struct BFaceMarch {
         // cell (loaded at the face, its latency stood before the face solve);
         // FP64 with the ionisation network has no registers left for it
         constexpr bool BN_AHEAD = !ION || sizeof(T) == 4;
-        auto bn_of = [&](int x) { return A.U.f[BX + D][base + (DIFF ? wrapc(x, nd) : x) * stride]; };
+        auto bn_of = [&](int x) { return at<O>(A.U.f[BX + D], base + (DIFF ? wrapc(x, nd) : x) * stride); };
         T bnn = BN_AHEAD ? bn_of(x0) : T(0);
         auto face = [&](int x) {
             const T bnx = BN_AHEAD ? bnn : bn_of(x);
@@ -699,16 +703,16 @@ struct BFaceMarch {
                        R, gm, ION ? gw[1] : gm, ION ? gw[2] : gm, ION, ydx, srl, srr, out);
             srl = srr;
             if (!DIFF) {
-                store_face(F, N, c, out);
+                store_face<O>(F, N, c, out);
             } else {
                 if (x < x1) {
-                    F[5 * N + c] = out[5];
-                    F[6 * N + c] = out[6];
+                    at<O>(F + 5 * N, c) = out[5];
+                    at<O>(F + 6 * N, c) = out[6];
                 }
                 if (x > x0) {
                     const int cm = base + (x - 1) * stride;
 #pragma unroll
-                    for (int v = 0; v < 5; v++) F[v * N + cm] = out[v] - prev[v][tid];
+                    for (int v = 0; v < 5; v++) at<O>(F + v * N, cm) = out[v] - prev[v][tid];
                 }
 #pragma unroll
                 for (int v = 0; v < 5; v++) prev[v][tid] = out[v];
@@ -757,7 +761,7 @@ struct FieldUpdateArgs {
 constexpr int UPD_NT = 256;
 constexpr int UPD_TX = 64;
 
-template <typename T>
+template <typename T, typename O>
 struct BFieldUpdate {
     static constexpr int NT = UPD_NT;
     static constexpr bool XCD = false;
@@ -774,7 +778,7 @@ struct BFieldUpdate {
         blk = xcd_band(blk, A.zt.ntx, A.zt.nty, (g.nz + A.zt.seg - 1) / A.zt.seg);
         if (!ztile_cell(g, A.zt, blk, tid, i, j, k0, k1)) return;
         const size_t N = (size_t)g.n;
-        const T dtdx = T(step_dt(A.a) / A.a.h);
+        const T dtdx = T(step_val<DTDX>(A.a));
         const T* Fx = A.Fx;
         const T* Fy = A.Fy;
         const T* Fz = A.Fz;
@@ -792,7 +796,7 @@ struct BFieldUpdate {
         const T* eyx = Fy + 6 * N;   // y faces, E along x
         const T* exy = Fx + 5 * N;   // x faces, E along y
         const T* exz = Fx + 6 * N;   // x faces, E along z
-        auto Ez = [&](int cc, int cym, int cxm) { return T(0.25) * (((exz[cym] + exz[cc]) + eyz[cxm]) + eyz[cc]); };
+        auto Ez = [&](int cc, int cym, int cxm) { return T(0.25) * (((at<O>(exz, cym) + at<O>(exz, cc)) + at<O>(eyz, cxm)) + at<O>(eyz, cc)); };
 
         // carried from the cell below: the Ex, Ey on its lower z edges, and the face
         // edge-field values of the current plane (and of the plane below at
@@ -802,14 +806,14 @@ struct BFieldUpdate {
         {
             int c = i + nx * j + nxy * k0;
             int zm = c + ((k0 == 0 ? nz - 1 : k0 - 1) - k0) * nxy;
-            ezx_c = ezx[c];
-            eyx_c = eyx[c];
-            ezy_c = ezy[c];
-            exy_c = exy[c];
-            eyx_ypm = eyx[zm + dyp];
-            exy_xpm = exy[zm + dxp];
-            Ex_c = T(0.25) * (((ezx[c + dym] + ezx_c) + eyx_c) + eyx[zm]);
-            Ey_c = T(0.25) * (((ezy[c + dxm] + ezy_c) + exy[zm]) + exy_c);
+            ezx_c = at<O>(ezx, c);
+            eyx_c = at<O>(eyx, c);
+            ezy_c = at<O>(ezy, c);
+            exy_c = at<O>(exy, c);
+            eyx_ypm = at<O>(eyx, zm + dyp);
+            exy_xpm = at<O>(exy, zm + dxp);
+            Ex_c = T(0.25) * (((at<O>(ezx, c + dym) + ezx_c) + eyx_c) + at<O>(eyx, zm));
+            Ey_c = T(0.25) * (((at<O>(ezy, c + dxm) + ezy_c) + at<O>(exy, zm)) + exy_c);
         }
         const T ra = T(A.rk.a), rb = T(A.rk.b);
         // two (FP64) or four (FP32) planes per loop trip: the loads of the
@@ -827,19 +831,19 @@ struct BFieldUpdate {
             if (!A.dbg) {
 #pragma unroll
                 for (int q = 0; q < 3; q++) {
-                    uo[q] = A.U.f[BX + q][c];
-                    so[q] = A.S.f[BX + q][c];
+                    uo[q] = at<O>(A.U.f[BX + q], c);
+                    so[q] = at<O>(A.S.f[BX + q], c);
                 }
             }
 
             // edge fields on the upper edges (Ex, Ey at z+1/2; Ex at y+1/2, Ey
             // at x+1/2): the same sums as for the carried lower edges
-            const T ezx_zp = ezx[zp], eyx_zp = eyx[zp], ezy_zp = ezy[zp], exy_zp = exy[zp];
-            const T eyx_yp = eyx[yp], exy_xp = exy[xp];
-            T Ex_yp = T(0.25) * (((ezx_c + ezx[yp]) + eyx_yp) + eyx_ypm);
-            T Ex_zp = T(0.25) * (((ezx[zp + dym] + ezx_zp) + eyx_zp) + eyx_c);
-            T Ey_xp = T(0.25) * (((ezy_c + ezy[xp]) + exy_xpm) + exy_xp);
-            T Ey_zp = T(0.25) * (((ezy[zp + dxm] + ezy_zp) + exy_c) + exy_zp);
+            const T ezx_zp = at<O>(ezx, zp), eyx_zp = at<O>(eyx, zp), ezy_zp = at<O>(ezy, zp), exy_zp = at<O>(exy, zp);
+            const T eyx_yp = at<O>(eyx, yp), exy_xp = at<O>(exy, xp);
+            T Ex_yp = T(0.25) * (((ezx_c + at<O>(ezx, yp)) + eyx_yp) + eyx_ypm);
+            T Ex_zp = T(0.25) * (((at<O>(ezx, zp + dym) + ezx_zp) + eyx_zp) + eyx_c);
+            T Ey_xp = T(0.25) * (((ezy_c + at<O>(ezy, xp)) + exy_xpm) + exy_xp);
+            T Ey_zp = T(0.25) * (((at<O>(ezy, zp + dxm) + ezy_zp) + exy_c) + exy_zp);
             T Ez_c = Ez(c, ym, xm);
             T Ez_xp = Ez(xp, xp + dym, c);
             T Ez_yp = Ez(yp, c, yp + dxm);
@@ -849,10 +853,10 @@ struct BFieldUpdate {
 
             if (A.dbg) {
 #pragma unroll
-                for (int q = 0; q < 3; q++) A.O.f[BX + q][c] = inc[q];
+                for (int q = 0; q < 3; q++) at<O>(A.O.f[BX + q], c) = inc[q];
             } else {
 #pragma unroll
-                for (int q = 0; q < 3; q++) A.O.f[BX + q][c] = (uo[q] + ra * (so[q] - uo[q])) + rb * inc[q];
+                for (int q = 0; q < 3; q++) at<O>(A.O.f[BX + q], c) = (uo[q] + ra * (so[q] - uo[q])) + rb * inc[q];
             }
             Ex_c = Ex_zp;
             Ey_c = Ey_zp;
@@ -1096,7 +1100,7 @@ __device__ __forceinline__ void tail_cell(const StepArgs& a, const ChemArgs& ch,
                                           double& hp)
 {
     const int ion = a.ion;
-    const double dt = step_dt(a);
+    const double dt = step_val<DT>(a);
     h2 = h2 > rho ? rho : h2;
     h2 = h2 < 0.0 ? 0.0 : h2;
     if (ion) {
@@ -1148,7 +1152,7 @@ __device__ __forceinline__ double tail_speed(const StepArgs& a, double rho, doub
 // cells (the upper face of its last cell, also formed by the next segment
 // from the same window) and the update reads one value per field instead of
 // two.
-template <typename T, int NQ>
+template <typename T, int NQ, typename O>
 struct BAdvFaceMarchY {
     static constexpr int NT = NTH;
     static constexpr bool XCD = false;
@@ -1177,7 +1181,7 @@ struct BAdvFaceMarchY {
         const int stride = g.nx;
         const int x0 = sgi * seg;
         const int x1 = min(x0 + seg, nd);
-        const T ydx = T(A.a.theta * (step_dt(A.a) / A.a.h));
+        const T ydx = T(step_val<YDX>(A.a));
         const int fld[8] = { RHO, MX, MY, MZ, EN, EI, H2, HP };
 
         // window: w[q][m] = field q of cell x-2+m (after the slide of face x)
@@ -1186,7 +1190,7 @@ struct BAdvFaceMarchY {
         for (int m = 0; m < 5; m++) {
             int cc = base + wrapc(x0 - 3 + m, nd) * stride;
 #pragma unroll
-            for (int q = 0; q < NQ; q++) w[q][m] = A.U.f[fld[q]][cc];
+            for (int q = 0; q < NQ; q++) w[q][m] = at<O>(A.U.f[fld[q]], cc);
         }
         // parabola of cell x0 - 1 (its right side is read by the first face),
         // the slope of cell x0 and the interface value at its lower face
@@ -1213,7 +1217,7 @@ struct BAdvFaceMarchY {
         auto fetch = [&](int x) {
             int cn = base + wrapc(x + 2, nd) * stride;
 #pragma unroll
-            for (int q = 0; q < NQ; q++) nw[q] = A.U.f[fld[q]][cn];
+            for (int q = 0; q < NQ; q++) nw[q] = at<O>(A.U.f[fld[q]], cn);
         };
         fetch(x0);
         // the flux of the lower face of the cell before x: in registers, or
@@ -1263,7 +1267,7 @@ struct BAdvFaceMarchY {
 #pragma unroll
                 for (int q = 0; q < NQ; q++) {
                     const T d = flux[q] - prev_of(q);
-                    A.F[q * N + c] = d;
+                    at<O>(A.F + q * N, c) = d;
                 }
             }
 #pragma unroll
@@ -1311,7 +1315,7 @@ struct AdvXZArgs {
     int seg;    // z cells per block
 };
 
-template <typename T, int Q0, int NQ, int MAXT>
+template <typename T, int Q0, int NQ, int MAXT, typename O>
 struct BAdvXZUpdate {
     static constexpr int NT = MAXT;
     static constexpr bool XCD = false;
@@ -1377,8 +1381,8 @@ struct BAdvXZUpdate {
         const size_t N = (size_t)g.n;
         const int base = i + g.nx * j;
         const int stride = g.nxy;
-        const T ydx = T(A.a.theta * (step_dt(A.a) / A.a.h));
-        const T dtdx = T(step_dt(A.a) / A.a.h);
+        const T ydx = T(step_val<YDX>(A.a));
+        const T dtdx = T(step_val<DTDX>(A.a));
         const int fld[8] = { RHO, MX, MY, MZ, EN, EI, H2, HP };
         const T ra = T(A.rk.a), rb = T(A.rk.b);
 
@@ -1391,11 +1395,11 @@ struct BAdvXZUpdate {
         for (int m = 0; m < 6; m++) {
             int cc = base + wrapc(x0 - 3 + m, nd) * stride;
 #pragma unroll
-            for (int q = 0; q < NQ; q++) w[q][m] = A.U.f[fld[Q0 + q]][cc];
+            for (int q = 0; q < NQ; q++) w[q][m] = at<O>(A.U.f[fld[Q0 + q]], cc);
             if (m == 2 || m == 3) {
-                vr[m - 2] = A.U.f[RHO][cc];
-                vm[m - 2] = A.U.f[MZ][cc];
-                if (!own_v) vx[m - 2] = A.U.f[MX][cc];
+                vr[m - 2] = at<O>(A.U.f[RHO], cc);
+                vm[m - 2] = at<O>(A.U.f[MZ], cc);
+                if (!own_v) vx[m - 2] = at<O>(A.U.f[MX], cc);
             }
         }
         auto velocity = [&]() {
@@ -1434,12 +1438,12 @@ struct BAdvXZUpdate {
         auto fetch = [&](int x) {
             int cn = base + wrapc(x + 3, nd) * stride;
 #pragma unroll
-            for (int q = 0; q < NQ; q++) nw[q] = A.U.f[fld[Q0 + q]][cn];
+            for (int q = 0; q < NQ; q++) nw[q] = at<O>(A.U.f[fld[Q0 + q]], cn);
             if (!own_v) {
                 int c1 = base + wrapc(x + 1, nd) * stride;
-                nvr = A.U.f[RHO][c1];
-                nvm = A.U.f[MZ][c1];
-                nvx = A.U.f[MX][c1];
+                nvr = at<O>(A.U.f[RHO], c1);
+                nvm = at<O>(A.U.f[MZ], c1);
+                nvx = at<O>(A.U.f[MX], c1);
             }
         };
         fetch(x0);
@@ -1523,8 +1527,8 @@ struct BAdvXZUpdate {
 #pragma unroll
             for (int q = 0; q < NQ; q++) {
                 const size_t o = (size_t)(Q0 + q) * N;
-                dy[q] = A.Fy[o + c];   // the y march stored the difference
-                sv[q] = A.S.f[fld[Q0 + q]][c];
+                dy[q] = at<O>(A.Fy + o, c);   // the y march stored the difference
+                sv[q] = at<O>(A.S.f[fld[Q0 + q]], c);
             }
             // upper face of cell x along z: between slots 2 and 3
             T Fup[NQ], nv[NQ];
@@ -1544,11 +1548,11 @@ struct BAdvXZUpdate {
             }
             if (own) {
 #pragma unroll
-                for (int q = 0; q < NQ; q++) A.O.f[fld[Q0 + q]][c] = nv[q];
+                for (int q = 0; q < NQ; q++) at<O>(A.O.f[fld[Q0 + q]], c) = nv[q];
                 if (Q0 == 0 && A.dbg) {
-                    A.O.f[BX][c] = T(0);
-                    A.O.f[BY][c] = T(0);
-                    A.O.f[BZ][c] = T(0);
+                    at<O>(A.O.f[BX], c) = T(0);
+                    at<O>(A.O.f[BY], c) = T(0);
+                    at<O>(A.O.f[BZ], c) = T(0);
                 }
             }
         };
@@ -1574,10 +1578,10 @@ struct BAdvXZUpdate {
 // L2; a small box pays the latency of one march instead of two.  (FP64 with the
 // H+ field keeps two launches: the second group's registers leave two waves per
 // SIMD, the first group alone three.)
-template <typename T, int NQ2, int MAXT>
+template <typename T, int NQ2, int MAXT, typename O>
 struct BAdvXZPair {
-    using G1 = BAdvXZUpdate<T, 0, 4, MAXT>;
-    using G2 = BAdvXZUpdate<T, 4, NQ2, MAXT>;
+    using G1 = BAdvXZUpdate<T, 0, 4, MAXT, O>;
+    using G2 = BAdvXZUpdate<T, 4, NQ2, MAXT, O>;
     static constexpr int NT = MAXT;
     static constexpr bool XCD = false;
     static constexpr int MINW = G1::MINW;
@@ -1596,7 +1600,7 @@ struct BAdvXZPair {
 // Tail of the step (after ADV) as a pass of its own: tail_cell on every cell,
 // validity flag, per-block CFL speed maximum.  mode: 1 = full tail, 0 = speed
 // only (state unchanged).
-template <typename T>
+template <typename T, typename O>
 struct BTail {
     static constexpr int NT = NTH;
     static constexpr bool XCD = false;
@@ -1621,22 +1625,22 @@ struct BTail {
             int i, j, k;
             decompose(g, c, i, j, k);
             const Fields<T>& U = A.U;
-            double rho = (double)U.f[RHO][c];
-            double mx = (double)U.f[MX][c], my = (double)U.f[MY][c], mz = (double)U.f[MZ][c];
-            double E = (double)U.f[EN][c];
-            double e = (double)U.f[EI][c];
-            double bx = 0.5 * ((double)U.f[BX][c] + (double)U.f[BX][nbr<0>(g, c, i, j, k, 1)]);
-            double by = 0.5 * ((double)U.f[BY][c] + (double)U.f[BY][nbr<1>(g, c, i, j, k, 1)]);
-            double bz = 0.5 * ((double)U.f[BZ][c] + (double)U.f[BZ][nbr<2>(g, c, i, j, k, 1)]);
+            double rho = (double)at<O>(U.f[RHO], c);
+            double mx = (double)at<O>(U.f[MX], c), my = (double)at<O>(U.f[MY], c), mz = (double)at<O>(U.f[MZ], c);
+            double E = (double)at<O>(U.f[EN], c);
+            double e = (double)at<O>(U.f[EI], c);
+            double bx = 0.5 * ((double)at<O>(U.f[BX], c) + (double)at<O>(U.f[BX], nbr<0>(g, c, i, j, k, 1)));
+            double by = 0.5 * ((double)at<O>(U.f[BY], c) + (double)at<O>(U.f[BY], nbr<1>(g, c, i, j, k, 1)));
+            double bz = 0.5 * ((double)at<O>(U.f[BZ], c) + (double)at<O>(U.f[BZ], nbr<2>(g, c, i, j, k, 1)));
             const int ion = A.a.ion;
-            double h2 = (double)U.f[H2][c];
-            double hp = ion ? (double)U.f[HP][c] : 0.0;
+            double h2 = (double)at<O>(U.f[H2], c);
+            double hp = ion ? (double)at<O>(U.f[HP], c) : 0.0;
             if (A.mode == 1) {
                 tail_cell<T>(A.a, A.ch, rho, mx, my, mz, bx, by, bz, E, e, h2, hp);
-                if (A.ch.cool) U.f[EN][c] = (T)E;
-                U.f[H2][c] = (T)h2;
-                U.f[EI][c] = (T)e;
-                if (ion) U.f[HP][c] = (T)hp;
+                if (A.ch.cool) at<O>(U.f[EN], c) = (T)E;
+                at<O>(U.f[H2], c) = (T)h2;
+                at<O>(U.f[EI], c) = (T)e;
+                if (ion) at<O>(U.f[HP], c) = (T)hp;
             }
             spd = tail_speed(A.a, rho, mx, my, mz, E, e, bx, by, bz, h2, hp, A.flags);
         }
@@ -1652,8 +1656,8 @@ struct BReduceDt {
     struct Args {
         const double* part;
         int nparts;
-        double cflh;
-        double* dt;
+        double cflh, h, theta;
+        double* dt;   // NDT values
     };
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
     {
@@ -1668,7 +1672,10 @@ struct BReduceDt {
         if (tid == 0) {
             double r = red[0];
             for (int w = 1; w < 16; w++) r = red[w] > r ? red[w] : r;
-            *A.dt = r > 0.0 ? A.cflh / r : 0.0;
+            const double dt = r > 0.0 ? A.cflh / r : 0.0;
+            A.dt[DT] = dt;
+            A.dt[DTDX] = dt / A.h;
+            A.dt[YDX] = A.theta * (dt / A.h);
         }
     }
 };

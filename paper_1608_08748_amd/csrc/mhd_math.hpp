@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 namespace mhd {
 
@@ -83,6 +84,19 @@ __device__ __forceinline__ void decompose(const Geo& g, int c, int& i, int& j, i
     i = c - row * g.nx;
     k = g.dy.div(row);
     j = row - k * g.ny;
+}
+
+// Value i of an array that starts at a kernel argument (the same address in
+// every lane).  With O = uint32_t the byte offset stays below 2^32 (arrays of
+// at most 4 GiB), so that the load takes the base from scalar registers and one
+// 32-bit offset serves every field of a cell; with 64-bit offsets each access
+// costs a 64-bit vector addition of its own (49 of 1190 instructions of the
+// FP32 x-row kernel).
+template <typename O, typename T>
+__device__ __forceinline__ T& at(T* p, int i)
+{
+    using C = std::conditional_t<std::is_const<T>::value, const char, char>;
+    return *reinterpret_cast<T*>(reinterpret_cast<C*>(p) + (O)((O)(unsigned)i * (O)sizeof(T)));
 }
 
 template <typename T> struct Fields { T* f[NF]; };
