@@ -284,6 +284,9 @@ ChemArgs chem_args(mhd_box* b)
     c.n_unit = b->p.n_unit_cm3;
     c.T_unit = b->p.T_unit_K;
     c.t_unit = b->p.t_unit_s;
+    // boxes without chemistry and cooling may have no units
+    c.n_inv = c.n_unit > 0.0 ? 1.0 / c.n_unit : 0.0;
+    c.e_rate = c.n_unit > 0.0 && c.T_unit > 0.0 ? c.t_unit / (c.n_unit * 1.380649e-16 * c.T_unit) : 0.0;
     return c;
 }
 

@@ -1112,12 +1112,12 @@ __device__ __forceinline__ void tail_cell(const StepArgs& a, const ChemArgs& ch,
         else h2 = chem_h2(ch, a.gamma, rho, e, h2, dt);
     }
     if (ch.cool) {
-        double en = ion ? cooled_e_ion(ch, rho, e, h2, hp, dt) : cooled_e(ch, a.gamma, rho, e, h2, dt);
+        double en = cooled_e(ch, gamma_cell(ion, a.gamma, rho, h2, hp), rho, e, h2, hp, dt);
         E += en - e;
         e = en;
         E = (double)(T)E;
     }
-    double K = 0.5 * (mx * mx + my * my + mz * mz) / rho;
+    double K = quot(0.5 * (mx * mx + my * my + mz * mz), rho);
     double M = 0.5 * (bx * bx + by * by + bz * bz);
     double ei = E - K - M;
     if (ei >= 1e-3 * E && (gamma_cell(ion, a.gamma, rho, h2, hp) - 1.0) * ei > M) e = ei;

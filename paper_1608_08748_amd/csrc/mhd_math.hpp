@@ -389,12 +389,29 @@ __device__ __forceinline__ void face_solve(T rl, T pl, T b1l, T b2l, T rr, T pr,
 
 // ---------------------------------------------------------------- FP64 per-cell physics
 
+// The per-cell physics of the tail is FP64 arithmetic on both precision paths
+// and bound the tail pass (470 us of a 6.1 ms FP32 step at 256^3 against 170 us
+// for its memory), so quotients share their reciprocals, powers share their
+// logarithms, and a rate with two branches selects its exponent and factor
+// before one exponential.  Quotients carry one residual correction, as close to
+// the exact value as a division rounds.
+
 struct ChemArgs {
     int on;     // chemistry stage
     int cool;   // heating/cooling stage
     int ion;    // ionisation network (reactions 5-8, H+ field, gamma_eff)
     double n_unit, T_unit, t_unit;
+    double n_inv;   // 1 / n_unit
+    double e_rate;  // t_unit / (n_unit k_B T_unit): erg cm^-3 s^-1 to code energy density per code time
 };
+
+// a / b from r = rcp_nr(b)
+__device__ __forceinline__ double quot(double a, double b, double r)
+{
+    const double q = a * r;
+    return fma(fma(-b, q, a), r, q);
+}
+__device__ __forceinline__ double quot(double a, double b) { return quot(a, b, rcp_nr(b)); }
 
 // Sec. 4.3: effective adiabatic index (5 n_H + 5 n_e + 7 n_H2) / (3 n_H +
 // 3 n_e + 5 n_H2) of a cell with the ionisation network (n_e = n_H+), the
@@ -403,7 +420,53 @@ __device__ __forceinline__ double gamma_cell(int ion, double gamma, double rho, 
 {
     if (!ion) return gamma;
     double nH = rho - h2 - hp, nH2 = 0.5 * h2, ne = hp;
-    return (5.0 * nH + 5.0 * ne + 7.0 * nH2) / (3.0 * nH + 3.0 * ne + 5.0 * nH2);
+    return quot(5.0 * nH + 5.0 * ne + 7.0 * nH2, 3.0 * nH + 3.0 * ne + 5.0 * nH2);
+}
+
+constexpr double LN10 = 2.302585092994045684;
+constexpr double INV_LN10 = 0.43429448190325182765;
+
+// number densities (cm^-3) and temperature of a cell: n_H = n_u (rho - h2 -
+// hp), T = T_u mu p / rho with the mean mass mu = 1 / (1 - x_H2/2 + x_H+)
+struct Gas {
+    double nH, nH2, ne, n, T, iT;
+};
+
+__device__ __forceinline__ Gas gas_state(const ChemArgs& ch, double gamma, double rho, double e, double h2, double hp)
+{
+    Gas g;
+    g.nH = ch.n_unit * (rho - h2 - hp);
+    g.nH2 = ch.n_unit * h2 / 2.0;
+    g.ne = ch.n_unit * hp;
+    g.n = g.nH + g.nH2 + g.ne;
+    g.T = quot(ch.T_unit * ((gamma - 1.0) * e), rho - 0.5 * h2 + hp);
+    g.iT = rcp_nr(g.T);
+    return g;
+}
+
+// formation rate C = k1' n n_H of reaction 1 as num / den
+__device__ __forceinline__ void formation(const Gas& g, double& num, double& den)
+{
+    const double t2 = 0.01 * g.T, st2 = root_nr(t2);
+    num = 3e-17 * st2 * g.n * g.nH;
+    den = 1.0 + 0.4 * st2 + 0.2 * t2 + 0.08 * t2 * t2;
+}
+
+// D = k2 n_H + k3 n_H2 + k4 of H2 (reactions 2-4, optically thin k4)
+__device__ __forceinline__ double h2_loss(const Gas& g)
+{
+    const double a = 6750.0 * g.iT, b = 7500.0 * g.iT;
+    const bool hot2 = g.T > 7390.0, hot3 = g.T > 7291.0;
+    const double k2 = (hot2 ? 6.11e-14 : 2.67e-15) * exp(hot2 ? -2.93e4 * g.iT : -(a * a));
+    const double k3 = (hot3 ? 5.22e-14 : 3.17e-15) * exp(hot3 ? -3.22e4 * g.iT : -(4060.0 * g.iT) - b * b);
+    return k2 * g.nH + k3 * g.nH2 + 3.3 * 1.7e-11;
+}
+
+// semi-implicit update (Sec. 2.7) of n with the creation rate num / den and
+// the loss rate D over ts: n + ts (C - D n) / (1 + ts D)
+__device__ __forceinline__ double semi_implicit(double n, double num, double den, double D, double ts)
+{
+    return n + quot(ts * (num - D * n * den), den * (1.0 + ts * D));
 }
 
 // rates of reactions 5-8 (appendix): cosmic-ray ionisation per H atom (s^-1),
@@ -413,54 +476,39 @@ __device__ __forceinline__ double rate_k6(double T)
 {
     const double l = log(T * 8.617333262e-5);
     const double c[9] = { -32.7, 13.5, -5.7, 1.5, -0.3, 3.4e-2, -2.6e-3, 1.1e-4, -2.1e-6 };
-    double s = 0.0, lp = 1.0;
+    double s = c[8];
 #pragma unroll
-    for (int i = 0; i < 9; i++) {
-        s += c[i] * lp;
-        lp *= l;
-    }
+    for (int i = 7; i >= 0; i--) s = s * l + c[i];
     return exp(s);
 }
 
-__device__ __forceinline__ double rate_k7(double T)
+__device__ __forceinline__ double rate_k7(double lnT)
 {
-    double x = log10(T);
-    double num = -10.78 + 4.68 * x - 0.87 * x * x + 0.08 * x * x * x - 3.87e-3 * x * x * x * x;
-    double den = 1.0 - 0.38 * x + 0.06 * x * x - 5.1e-3 * x * x * x + 2.4e-4 * x * x * x * x;
-    return pow(10.0, num / den);
+    const double x = lnT * INV_LN10;
+    const double num = -10.78 + x * (4.68 + x * (-0.87 + x * (0.08 + x * -3.87e-3)));
+    const double den = 1.0 + x * (-0.38 + x * (0.06 + x * (-5.1e-3 + x * 2.4e-4)));
+    return exp(LN10 * quot(num, den));
 }
 
-__device__ __forceinline__ double rate_k8(double T)
+__device__ __forceinline__ double rate_k8(double lnT)
 {
-    double inner = 1.0 + 5.087e2 * pow(T, 1.586e-2) * pow(10.0, -1.8892 - 4.4e-5 * log10(T));
-    return 12.25e-14 / (1.0 + 8.074e-6 * pow(10.0, 2.756) * inner);
+    // T^0.01586 10^(-1.8892 - 4.4e-5 log10 T) as one exponential; the last
+    // factor is 10^2.756
+    const double inner = 1.0 + 5.087e2 * exp((1.586e-2 - 4.4e-5) * lnT - 1.8892 * LN10);
+    return quot(12.25e-14, 1.0 + 8.074e-6 * 570.1642722807472 * inner);
 }
 
 // Sec. 2.7 with the appendix rates of reactions 1-4 (optically thin k4)
-__device__ double chem_h2(const ChemArgs& ch, double gamma, double rho, double e, double h2, double dt)
+__device__ __forceinline__ double chem_h2(const ChemArgs& ch, double gamma, double rho, double e, double h2, double dt)
 {
-    double p = (gamma - 1.0) * e;
-    double xh2 = h2 / rho;
-    double mu = 1.0 / (1.0 - 0.5 * xh2);
-    double T = ch.T_unit * mu * p / rho;
-    double nH = ch.n_unit * (rho - h2);
-    double nH2 = ch.n_unit * h2 / 2.0;
-    double n = nH + nH2;
-    double t2 = T / 100.0;
-    double st2 = sqrt(t2);
-    double k1b = 3e-17 * st2 / (1.0 + 0.4 * st2 + 0.2 * t2 + 0.08 * t2 * t2);
-    double k2 = (T > 7390.0) ? 6.11e-14 * exp(-2.93e4 / T) : 2.67e-15 * exp(-(6750.0 / T) * (6750.0 / T));
-    double k3 = (T > 7291.0) ? 5.22e-14 * exp(-3.22e4 / T)
-                             : 3.17e-15 * exp(-(4060.0 / T) - (7500.0 / T) * (7500.0 / T));
-    double k4 = 3.3 * 1.7e-11;
-    double C = k1b * n * nH;
-    double Dd = k2 * nH + k3 * nH2 + k4;
-    double ts = dt * ch.t_unit;
-    double nn = nH2 + ts * (C - Dd * nH2) / (1.0 + ts * Dd);
-    double nmax = ch.n_unit * rho / 2.0;
+    const Gas g = gas_state(ch, gamma, rho, e, h2, 0.0);
+    double num, den;
+    formation(g, num, den);
+    double nn = semi_implicit(g.nH2, num, den, h2_loss(g), dt * ch.t_unit);
+    const double nmax = ch.n_unit * rho / 2.0;
     nn = nn > nmax ? nmax : nn;
     nn = nn < 0.0 ? 0.0 : nn;
-    return 2.0 * nn / ch.n_unit;
+    return 2.0 * quot(nn, ch.n_unit, ch.n_inv);
 }
 
 // Sec. 2 stage 5 and Sec. 2.8 with the appendix heating and cooling of
@@ -471,49 +519,52 @@ __device__ double chem_h2(const ChemArgs& ch, double gamma, double rho, double e
 // n_H2 L_H / (1 + L_H / L_L) of reactions 2 and 3.  In reaction 3's low-density
 // limit k_H = k_H2 = 6.29e-15 * 1.38 f(T) / f(4500), f = sqrt(T) a exp(-a),
 // a = 1 + 1 / (k_B T) with k_B T in eV, evaluated in logarithms.  Returns
-// Gamma - Lambda.
-__device__ double heat_cool(const ChemArgs& ch, double gamma, double rho, double e, double h2)
+// Gamma - Lambda; with the ionisation network n = n_H + n_H2 + n_H+, plus
+// cosmic-ray heating 1.92e-28 n and collisional-ionisation cooling 2.18e-11
+// erg k6 n_H n_e.
+__device__ __forceinline__ double heat_cool(int ion, const Gas& g)
 {
-    const double kb_ev = 8.617333262e-5;
-    double p = (gamma - 1.0) * e;
-    double mu = 1.0 / (1.0 - 0.5 * (h2 / rho));
-    double T = ch.T_unit * mu * p / rho;
-    double nH = ch.n_unit * (rho - h2);
-    double nH2 = ch.n_unit * h2 / 2.0;
-    double n = nH + nH2;
-    double x = log10(T / 1e4);
-    double t2 = T / 100.0;
-    double st2 = sqrt(t2);
-    double k1b = 3e-17 * st2 / (1.0 + 0.4 * st2 + 0.2 * t2 + 0.08 * t2 * t2);
-    double ncr = pow(10.0, 4.0 - 0.416 * x - 0.327 * x * x);
-    double g1 = 7.2e-12 * (k1b * n * nH) / (1.0 + ncr / n);
-    double g4 = 6.4e-13 * (3.3 * 1.7e-11) * nH2;
-    double lh2 = (T > 1087.0) ? 3.9e-19 * exp(-6118.0 / T) : pow(10.0, -19.24 + 0.474 * x - 1.247 * x * x);
-    double fl2 = (T > 4031.0) ? 1.38e-22 * exp(-9243.0 / T) : pow(10.0, -22.9 - 0.553 * x - 1.148 * x * x);
-    double ll2 = (pow(nH2, 0.77) + 1.2 * pow(nH, 0.77)) * fl2;
-    double l2 = nH2 * lh2 / (1.0 + lh2 / ll2);
-    double a = 1.0 + 1.0 / (kb_ev * T);
-    const double a45 = 1.0 + 1.0 / (kb_ev * 4500.0);
-    double lnf = 0.5 * log(T) + log(a) - a;
-    double lnf45 = 0.5 * log(4500.0) + log(a45) - a45;
-    double ln_ll3 = log(8.18e-13) + log(n) + log(6.29e-15 * 1.38) + lnf - lnf45;
-    double ln_lh3 = log(1.1e-13) - 6744.0 / T;
-    double l3 = nH2 * exp(ln_lh3) / (1.0 + exp(ln_lh3 - ln_ll3));
-    return (g1 + g4) - (l2 + l3);
+    const double ikb_ev = 1.0 / 8.617333262e-5;
+    const double lnT = log(g.T);
+    const double x = (lnT - 4.0 * LN10) * INV_LN10;
+    double num, den;
+    formation(g, num, den);
+    const double ncr = exp(LN10 * (4.0 - 0.416 * x - 0.327 * x * x));
+    // num / den / (1 + n_cr / n)
+    const double g1 = 7.2e-12 * quot(num * g.n, den * (g.n + ncr));
+    const double g4 = 6.4e-13 * (3.3 * 1.7e-11) * g.nH2;
+    const bool hoth = g.T > 1087.0, hotl = g.T > 4031.0;
+    const double lh2 = (hoth ? 3.9e-19 : 1.0) * exp(hoth ? -6118.0 * g.iT : LN10 * (-19.24 + 0.474 * x - 1.247 * x * x));
+    const double fl2 = (hotl ? 1.38e-22 : 1.0) * exp(hotl ? -9243.0 * g.iT : LN10 * (-22.9 - 0.553 * x - 1.148 * x * x));
+    const double ll2 = (exp(0.77 * log(g.nH2)) + 1.2 * exp(0.77 * log(g.nH))) * fl2;
+    const double l2 = g.nH2 * quot(lh2 * ll2, lh2 + ll2);   // n_H2 L_H / (1 + L_H / L_L)
+    const double a = 1.0 + ikb_ev * g.iT;
+    const double a45 = 1.0 + 1.0 / (8.617333262e-5 * 4500.0);
+    const double lnf = 0.5 * lnT + log(a * g.n) - a;   // with the log(n) of the limit
+    const double lnf45 = 0.5 * log(4500.0) + log(a45) - a45;
+    const double ln_ll3 = log(8.18e-13) + log(6.29e-15 * 1.38) + lnf - lnf45;
+    const double ln_lh3 = log(1.1e-13) - 6744.0 * g.iT;
+    // the second exponential is far from overflow where the first is not zero
+    const double l3 = g.nH2 * quot(exp(ln_lh3), 1.0 + exp(fmin(ln_lh3 - ln_ll3, 600.0)));
+    double gain = g1 + g4, loss = l2 + l3;
+    if (ion) {
+        gain += 1.92e-28 * g.n;
+        loss += 2.18e-11 * rate_k6(g.T) * g.nH * g.ne;
+    }
+    return gain - loss;
 }
 
 // explicit Euler step of the internal energy over dt with Gamma - Lambda
 // frozen; energy unit n_unit k_B T_unit; cooling stops at the internal energy
 // of 10 K, or at e where the cell is already colder
-__device__ double cooled_e(const ChemArgs& ch, double gamma, double rho, double e, double h2, double dt)
+__device__ __forceinline__ double cooled_e(const ChemArgs& ch, double gamma, double rho, double e, double h2, double hp,
+                                           double dt)
 {
-    const double kb = 1.380649e-16, t_floor = 10.0;
-    double eu = ch.n_unit * kb * ch.T_unit;
-    double de = dt * ch.t_unit * heat_cool(ch, gamma, rho, e, h2) / eu;
-    double mu = 1.0 / (1.0 - 0.5 * (h2 / rho));
-    double efloor = rho * t_floor / (ch.T_unit * mu * (gamma - 1.0));
-    double lo = e < efloor ? e : efloor;
-    double en = e + de;
+    const Gas g = gas_state(ch, gamma, rho, e, h2, hp);
+    const double de = dt * ch.e_rate * heat_cool(ch.ion, g);
+    const double efloor = quot(10.0 * (rho - 0.5 * h2 + hp), ch.T_unit * (gamma - 1.0));
+    const double lo = e < efloor ? e : efloor;
+    const double en = e + de;
     return en < lo ? lo : en;
 }
 
@@ -521,109 +572,43 @@ __device__ double cooled_e(const ChemArgs& ch, double gamma, double rho, double 
 // n_H2 and n_H+ = n_e from the state at the start of the step, n_H = n_u (rho
 // - h2 - hp); H2 clamped to [0, n_u (rho - hp) / 2], then H+ to [0, n_u (rho -
 // h2')]; temperature from gamma_eff and the mean mass 1 / (1 - x_H2/2 + x_H+)
-__device__ void chem_ion(const ChemArgs& ch, double rho, double e, double h2, double hp, double dt, double& h2_out,
-                         double& hp_out)
+__device__ __forceinline__ void chem_ion(const ChemArgs& ch, double rho, double e, double h2, double hp, double dt,
+                                         double& h2_out, double& hp_out)
 {
-    double gam = gamma_cell(1, 0.0, rho, h2, hp);
-    double p = (gam - 1.0) * e;
-    double mu = 1.0 / (1.0 - 0.5 * (h2 / rho) + hp / rho);
-    double T = ch.T_unit * mu * p / rho;
-    double nH = ch.n_unit * (rho - h2 - hp);
-    double nH2 = ch.n_unit * h2 / 2.0;
-    double ne = ch.n_unit * hp;
-    double n = nH + nH2 + ne;
-    double ts = dt * ch.t_unit;
-    double t2 = T / 100.0;
-    double st2 = sqrt(t2);
-    double k1b = 3e-17 * st2 / (1.0 + 0.4 * st2 + 0.2 * t2 + 0.08 * t2 * t2);
-    double k2 = (T > 7390.0) ? 6.11e-14 * exp(-2.93e4 / T) : 2.67e-15 * exp(-(6750.0 / T) * (6750.0 / T));
-    double k3 = (T > 7291.0) ? 5.22e-14 * exp(-3.22e4 / T)
-                             : 3.17e-15 * exp(-(4060.0 / T) - (7500.0 / T) * (7500.0 / T));
-    double k4 = 3.3 * 1.7e-11;
-    double C = k1b * n * nH;
-    double Dd = k2 * nH + k3 * nH2 + k4;
-    double m2 = nH2 + ts * (C - Dd * nH2) / (1.0 + ts * Dd);
-    double m2max = ch.n_unit * (rho - hp) / 2.0;
+    const Gas g = gas_state(ch, gamma_cell(1, 0.0, rho, h2, hp), rho, e, h2, hp);
+    const double ts = dt * ch.t_unit;
+    double num, den;
+    formation(g, num, den);
+    double m2 = semi_implicit(g.nH2, num, den, h2_loss(g), ts);
+    const double m2max = ch.n_unit * (rho - hp) / 2.0;
     m2 = m2 > m2max ? m2max : m2;
     m2 = m2 < 0.0 ? 0.0 : m2;
-    double Ci = 6e-18 * nH + rate_k6(T) * nH * ne;
-    double Di = (rate_k7(T) + rate_k8(T)) * ne;
-    double mi = ne + ts * (Ci - Di * ne) / (1.0 + ts * Di);
-    double h2n = 2.0 * m2 / ch.n_unit;
-    double mimax = ch.n_unit * (rho - h2n);
+    const double lnT = log(g.T);
+    const double Ci = 6e-18 * g.nH + rate_k6(g.T) * g.nH * g.ne;
+    const double Di = (rate_k7(lnT) + rate_k8(lnT)) * g.ne;
+    double mi = semi_implicit(g.ne, Ci, 1.0, Di, ts);
+    const double h2n = 2.0 * quot(m2, ch.n_unit, ch.n_inv);
+    const double mimax = ch.n_unit * (rho - h2n);
     mi = mi > mimax ? mimax : mi;
     mi = mi < 0.0 ? 0.0 : mi;
     h2_out = h2n;
-    hp_out = mi / ch.n_unit;
+    hp_out = quot(mi, ch.n_unit, ch.n_inv);
 }
 
-// heating/cooling with the ionisation network: the terms of reactions 1-4
-// with gamma_eff, the ion mean mass and n = n_H + n_H2 + n_H+, plus cosmic-ray
-// heating 1.92e-28 n and collisional-ionisation cooling 2.18e-11 erg k6 n_H n_e
-__device__ double heat_cool_ion(const ChemArgs& ch, double rho, double e, double h2, double hp)
+// Sec. 2.3: the speed sum of the CFL rule for one cell (FP64), v + b + c + c_a
+// + c_s + c_f; c_f^2 + c_s^2 = c^2 + b^2 and c_f c_s = c c_a, so c_f + c_s =
+// sqrt(c^2 + b^2 + 2 c c_a), without the differences of the two speeds
+__device__ __forceinline__ double cell_speed(double gamma, double rho, double mx, double my, double mz, double e,
+                                             double bx, double by, double bz)
 {
-    const double kb_ev = 8.617333262e-5;
-    double gam = gamma_cell(1, 0.0, rho, h2, hp);
-    double p = (gam - 1.0) * e;
-    double mu = 1.0 / (1.0 - 0.5 * (h2 / rho) + hp / rho);
-    double T = ch.T_unit * mu * p / rho;
-    double nH = ch.n_unit * (rho - h2 - hp);
-    double nH2 = ch.n_unit * h2 / 2.0;
-    double ne = ch.n_unit * hp;
-    double n = nH + nH2 + ne;
-    double x = log10(T / 1e4);
-    double t2 = T / 100.0;
-    double st2 = sqrt(t2);
-    double k1b = 3e-17 * st2 / (1.0 + 0.4 * st2 + 0.2 * t2 + 0.08 * t2 * t2);
-    double ncr = pow(10.0, 4.0 - 0.416 * x - 0.327 * x * x);
-    double g1 = 7.2e-12 * (k1b * n * nH) / (1.0 + ncr / n);
-    double g4 = 6.4e-13 * (3.3 * 1.7e-11) * nH2;
-    double lh2 = (T > 1087.0) ? 3.9e-19 * exp(-6118.0 / T) : pow(10.0, -19.24 + 0.474 * x - 1.247 * x * x);
-    double fl2 = (T > 4031.0) ? 1.38e-22 * exp(-9243.0 / T) : pow(10.0, -22.9 - 0.553 * x - 1.148 * x * x);
-    double ll2 = (pow(nH2, 0.77) + 1.2 * pow(nH, 0.77)) * fl2;
-    double l2 = nH2 * lh2 / (1.0 + lh2 / ll2);
-    double a = 1.0 + 1.0 / (kb_ev * T);
-    const double a45 = 1.0 + 1.0 / (kb_ev * 4500.0);
-    double lnf = 0.5 * log(T) + log(a) - a;
-    double lnf45 = 0.5 * log(4500.0) + log(a45) - a45;
-    double ln_ll3 = log(8.18e-13) + log(n) + log(6.29e-15 * 1.38) + lnf - lnf45;
-    double ln_lh3 = log(1.1e-13) - 6744.0 / T;
-    double l3 = nH2 * exp(ln_lh3) / (1.0 + exp(ln_lh3 - ln_ll3));
-    double g5 = 1.92e-28 * n;
-    double l6 = 2.18e-11 * rate_k6(T) * nH * ne;
-    return (g1 + g4 + g5) - (l2 + l3 + l6);
-}
-
-__device__ double cooled_e_ion(const ChemArgs& ch, double rho, double e, double h2, double hp, double dt)
-{
-    const double kb = 1.380649e-16, t_floor = 10.0;
-    double eu = ch.n_unit * kb * ch.T_unit;
-    double de = dt * ch.t_unit * heat_cool_ion(ch, rho, e, h2, hp) / eu;
-    double mu = 1.0 / (1.0 - 0.5 * (h2 / rho) + hp / rho);
-    double efloor = rho * t_floor / (ch.T_unit * mu * (gamma_cell(1, 0.0, rho, h2, hp) - 1.0));
-    double lo = e < efloor ? e : efloor;
-    double en = e + de;
-    return en < lo ? lo : en;
-}
-
-// Sec. 2.3: the speed sum of the CFL rule for one cell (FP64)
-__device__ double cell_speed(double gamma, double rho, double mx, double my, double mz, double e, double bx,
-                             double by, double bz)
-{
-    double vx = mx / rho, vy = my / rho, vz = mz / rho;
-    double v = sqrt(vx * vx + vy * vy + vz * vz);
-    double p = (gamma - 1.0) * e;
-    double c2 = gamma * p / rho;
-    double ca2 = bx * bx / rho;
-    double b2 = (bx * bx + by * by + bz * bz) / rho;
-    double s = c2 + b2;
-    double disc = s * s - 4.0 * c2 * ca2;
-    disc = disc < 0.0 ? 0.0 : disc;
-    double sd = sqrt(disc);
-    double cf2 = 0.5 * (s + sd);
-    double cs2 = 0.5 * (s - sd);
-    cs2 = cs2 < 0.0 ? 0.0 : cs2;
-    return v + sqrt(b2) + sqrt(c2) + sqrt(ca2) + sqrt(cs2) + sqrt(cf2);
+    const double rs = rsqrt_nr(rho);   // 1 / sqrt(rho)
+    const double v = root_nr(mx * mx + my * my + mz * mz) * (rs * rs);
+    const double c = root_nr(gamma * ((gamma - 1.0) * e)) * rs;
+    const double ca = fabs(bx) * rs;
+    const double b = root_nr(bx * bx + by * by + bz * bz) * rs;
+    const double s = v + b + c + ca + root_nr(c * c + b * b + 2.0 * c * ca);
+    // squares beyond the range of the refined roots: no step is short enough
+    return s <= 1e300 ? s : INFINITY;
 }
 
 __device__ __forceinline__ double wave_max(double v)
