@@ -152,15 +152,19 @@ template <typename T> struct Par { T qL, qR, dq, q6; };
 
 // Step 1: limited central difference (min of the three candidates, sign of
 // the central difference; zero at extrema)
-template <typename T>
-__device__ __forceinline__ T limited_slope(T qm, T q0, T qp)
+__device__ __forceinline__ double limited_slope(double qm, double q0, double qp)
 {
-    T dq = T(0.5) * (qp - qm);
-    // the same minimum either way: one product less in FP64, a three-way
-    // minimum instruction in FP32
-    T m = sizeof(T) == 8 ? fmin(fabs(dq), T(2) * fmin(fabs(qp - q0), fabs(q0 - qm)))
-                         : fmin(fmin(fabs(dq), T(2) * fabs(qp - q0)), T(2) * fabs(q0 - qm));
-    return ((qp - q0) * (q0 - qm) > T(0)) ? copysign(m, dq) : T(0);
+    double dq = 0.5 * (qp - qm);
+    double m = fmin(fabs(dq), 2.0 * fmin(fabs(qp - q0), fabs(q0 - qm)));
+    return ((qp - q0) * (q0 - qm) > 0.0) ? copysign(m, dq) : 0.0;
+}
+// FP32: the median of zero and two numbers is the smaller one of the same sign,
+// or zero, so two median instructions give the same value in 7 instructions
+// instead of 11 (also where the product of the two differences underflows)
+__device__ __forceinline__ float limited_slope(float qm, float q0, float qp)
+{
+    const float lim = 2.0f * __builtin_amdgcn_fmed3f(0.0f, qp - q0, q0 - qm);
+    return __builtin_amdgcn_fmed3f(0.0f, 0.5f * (qp - qm), lim);
 }
 
 // Step 1: fourth-order interface value q_{j+1/2} = 1/2 (q_j + q_{j+1}) - 1/6 (dm_{j+1} - dm_j)
