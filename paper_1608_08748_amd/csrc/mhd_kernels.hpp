@@ -202,7 +202,8 @@ __global__ __launch_bounds__(Body::NT) __attribute__((amdgpu_waves_per_eu(MinWav
     for (;;) {
         if (threadIdx.x == 0) taken = atomicAdd(next, chunk);
         __syncthreads();
-        const int c0 = taken;
+        // the same in every lane: the box's arguments come in scalar registers
+        const int c0 = __builtin_amdgcn_readfirstlane(taken);
         if (c0 >= total) break;
         const int c1 = min(c0 + chunk, total);
         for (int blk = c0; blk < c1; blk++) {

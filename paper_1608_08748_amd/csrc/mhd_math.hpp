@@ -92,11 +92,15 @@ __device__ __forceinline__ void decompose(const Geo& g, int c, int& i, int& j, i
 // 32-bit offset serves every field of a cell; with 64-bit offsets each access
 // costs a 64-bit vector addition of its own (49 of 1190 instructions of the
 // FP32 x-row kernel).
+// The global address space is stated because the pointers of a multi-box launch
+// come from its table in memory, where the compiler would take them for
+// generic ones (flat loads, which also wait for the LDS).
+template <typename T> using Global = __attribute__((address_space(1))) T;
 template <typename O, typename T>
-__device__ __forceinline__ T& at(T* p, int i)
+__device__ __forceinline__ Global<T>& at(T* p, int i)
 {
     using C = std::conditional_t<std::is_const<T>::value, const char, char>;
-    return *reinterpret_cast<T*>(reinterpret_cast<C*>(p) + (O)((O)(unsigned)i * (O)sizeof(T)));
+    return *(Global<T>*)((Global<C>*)p + (O)((O)(unsigned)i * (O)sizeof(T)));
 }
 
 template <typename T> struct Fields { T* f[NF]; };
