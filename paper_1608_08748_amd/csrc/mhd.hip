@@ -81,6 +81,7 @@ struct mhd_box {
     // faces along y and z, the ADV faces along y, the fused ADV update and the
     // face-field update along z
     int seg_fy, seg_fz, seg_ay, seg_xz, seg_b;
+    bool stream;       // kernel outputs go past the caches (streamed())
     // per-launch event timing (mhd_set_timing)
     int timing;
     int nev;
@@ -152,6 +153,12 @@ bool valid_params(const mhd_params* p)
 size_t face_values(bool ion) { return ion ? NFACE + 1 : NFACE; }
 
 void march_segments(mhd_box* b, double share);
+
+// whether a launch over fields of this many bytes streams its outputs: the
+// step's arrays together (about 54 fields) then hold the 256 MB Infinity Cache
+// several times.  Level at 120^3 FP64 (13.8 MB) and between 128^3 (8.4 MB, 1.5%
+// slower) and 144^3 FP32 (11.9 MB, 1% faster).
+bool streamed(double field_bytes) { return field_bytes > 12e6; }
 
 // chunks of the totals' partial sums: of 4096 cells (16 per thread), and at
 // most 512, one wave's eight loads per lane in the last sum
@@ -225,6 +232,7 @@ void box_bind(mhd_box* b, const mhd_params* p, const Layout& L)
     }
     b->cur[0] = b->cur[1] = b->cur[2] = 0;
     march_segments(b, 1.0);
+    b->stream = streamed((double)b->g.n * (double)b->esz);
     b->timing = 0;
     b->nev = 0;
     b->ev_ready = 0;
@@ -334,11 +342,11 @@ int timing_collect(mhd_box* b)
 // reach (more than 2^29 cells in FP64, 2^30 in FP32)
 bool wide_fields(const mhd_box* b) { return (uint64_t)b->g.n * b->esz > ((uint64_t)1 << 32); }
 
-// sends each launch of the program straight to the box's stream; O: the type of
-// the kernels' byte offsets
-template <typename O>
+// sends each launch of the program straight to the box's stream; O: how the
+// kernels reach the fields (Near, Streamed or Far)
+template <class O>
 struct OneEmit {
-    using Off = O;
+    using Access = O;
     mhd_box* b;
     template <class Body>
     void launch(int cls, int blocks, size_t shm, const typename Body::Args& a, int parts = 1)
@@ -417,9 +425,9 @@ int go_persist(const void* tab, const int* bstart, int nbox, int blocks, size_t 
     }
 }
 
-template <typename O>
+template <class O>
 struct MultiEmit {
-    using Off = O;
+    using Access = O;
     std::vector<MultiRec>* recs;
     size_t k;        // program position within the current box
     bool first;      // the first box defines the program
@@ -575,7 +583,7 @@ template <typename T, bool ION, class Emit>
 void emit_nonadv_substage_t(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout, const StepArgs& a, RK rk,
                             int dbg, bool first)
 {
-    using O = typename Emit::Off;
+    using O = typename Emit::Access;
     Fields<T> in = view<T>(b, sin.h, sin.m, sin.b);
     Fields<T> S = view<T>(b, sS.h, sS.m, sS.b);
     Fields<T> out = view<T>(b, sout.h, sout.m, sout.b);
@@ -650,7 +658,7 @@ void emit_nonadv_substage(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout, 
 template <typename T, int NQ, class Emit>
 void emit_adv_face(mhd_box* b, Emit& e, const Fields<T>& in, const StepArgs& a)
 {
-    using O = typename Emit::Off;
+    using O = typename Emit::Access;
     typename BAdvFaceMarchY<T, NQ, O>::Args ma;
     ma.g = b->g;
     ma.U = cview(in);
@@ -666,7 +674,7 @@ void emit_adv_face(mhd_box* b, Emit& e, const Fields<T>& in, const StepArgs& a)
 template <typename T, int NT, class Emit>
 void emit_adv_xz(Emit& e, const AdvXZArgs<T>& xa, bool ion)
 {
-    using O = typename Emit::Off;
+    using O = typename Emit::Access;
     auto shm = [](int nv, int nq) { return (size_t)2 * (nv + 2 * nq) * NT * sizeof(T); };
     const int both = (xa.tiles + 7) / 8 * 16;
     if (!ion) {
@@ -758,7 +766,7 @@ void emit_reduce_dt(mhd_box* b, Emit& e, int nparts)
 template <typename T, class Emit>
 void emit_tail(mhd_box* b, Emit& e, const StepArgs& a, int mode)
 {
-    using O = typename Emit::Off;
+    using O = typename Emit::Access;
     typename BTail<T, O>::Args ta;
     ta.g = b->g;
     ta.U = view<T>(b, b->cur[GH], b->cur[GM], b->cur[GB]);
@@ -873,10 +881,13 @@ template <class F>
 void with_emit(mhd_box* b, F&& f)
 {
     if (wide_fields(b)) {
-        OneEmit<uint64_t> e{ b };
+        OneEmit<Far> e{ b };
+        f(e);
+    } else if (b->stream) {
+        OneEmit<Streamed> e{ b };
         f(e);
     } else {
-        OneEmit<uint32_t> e{ b };
+        OneEmit<Near> e{ b };
         f(e);
     }
 }
@@ -1426,7 +1437,7 @@ int server_admit(mhd_server* sv)
 }
 
 // one step of every active box, merged into one launch per program position
-template <typename T, typename O>
+template <typename T, class O>
 int server_step(mhd_server* sv, int half)
 {
     sv->recs.clear();
@@ -1479,6 +1490,20 @@ int server_step(mhd_server* sv, int half)
     return launch_status();
 }
 
+// the round in the form that fits the boxes in flight
+template <typename T>
+int server_round(mhd_server* sv, int half)
+{
+    bool far = false;
+    double cells = 0.0;
+    for (const mhd_server::Active& a : sv->active) {
+        far = far || wide_fields(a.box);
+        cells += (double)a.box->g.n;
+    }
+    if (far) return server_step<T, Far>(sv, half);
+    return streamed(cells * sizeof(T)) ? server_step<T, Streamed>(sv, half) : server_step<T, Near>(sv, half);
+}
+
 double* ret_slot(mhd_server* sv, int half, int k)
 {
     return reinterpret_cast<double*>(sv->htab + 2 * SERVER_TAB_BYTES +
@@ -1528,12 +1553,7 @@ int server_progress(mhd_server* sv, int* nact, int* npend)
     const int half = (int)(sv->rounds & 1);
     bool launched = false;
     if (!sv->active.empty()) {
-        bool wide = false;
-        for (const mhd_server::Active& a : sv->active) wide = wide || wide_fields(a.box);
-        if (sv->p.precision == MHD_FP64)
-            st = wide ? server_step<double, uint64_t>(sv, half) : server_step<double, uint32_t>(sv, half);
-        else
-            st = wide ? server_step<float, uint64_t>(sv, half) : server_step<float, uint32_t>(sv, half);
+        st = sv->p.precision == MHD_FP64 ? server_round<double>(sv, half) : server_round<float>(sv, half);
         if (st) return st;
         // boxes that have run their steps leave the round: their totals and
         // flags go to pinned slots behind the round on the stream, and (unless
@@ -1696,7 +1716,7 @@ int mhd_get_state(mhd_box* b, double* cons_out)
 int mhd_get_potential(mhd_box* b, double* phi_out)
 {
     if (!b || !phi_out || !b->grav) return MHD_EINVAL;
-    OneEmit<uint32_t> e{ b };   // the Poisson kernels index by cell
+    OneEmit<Near> e{ b };   // the Poisson kernels index by cell
     const size_t N = (size_t)b->g.n;
     if (b->prec == MHD_FP64) {
         emit_poisson<double>(b, e);

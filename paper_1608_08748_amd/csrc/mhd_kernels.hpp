@@ -234,7 +234,7 @@ __global__ __launch_bounds__(Body::NT) __attribute__((amdgpu_waves_per_eu(MinWav
 // and, with the ionisation network, the H2 and H+ densities
 template <typename T> struct Raw { T rho, mn, m1, m2, e, b1, b1p, b2, b2p, h2, hp; };
 
-template <typename T, int D, bool ION, typename O>
+template <typename T, int D, bool ION, class O>
 __device__ __forceinline__ void raw_load(const CFields<T>& U, int c, int c1, int c2, Raw<T>& r)
 {
     constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
@@ -275,13 +275,6 @@ __device__ __forceinline__ void raw_prim(const Raw<T>& r, double gamma, T q[6], 
 }
 
 // ---------------------------------------------------------------- NONADV faces
-
-template <typename O, typename T>
-__device__ __forceinline__ void store_face(T* __restrict__ F, size_t N, int c, const T out[7])
-{
-#pragma unroll
-    for (int q = 0; q < 7; q++) at<O>(F + q * N, c) = out[q];
-}
 
 template <typename T>
 struct FaceArgs {
@@ -340,7 +333,7 @@ template <typename T> struct FluxDiff { static constexpr bool v = sizeof(T) == 4
 // needs one barrier.
 constexpr int XROW_SLOTS = 18;
 
-template <typename T, int MAXT, bool ION, typename O>
+template <typename T, int MAXT, bool ION, class O>
 struct BFaceXRows {
     static constexpr int NT = MAXT;
     static constexpr bool XCD = false;
@@ -494,8 +487,8 @@ struct BFaceXRows {
                         sc[q] = at<O>(A.S.f[upd[q]], c);
                     }
                 }
-                at<O>(A.F + 5 * N, c) = out[5];
-                at<O>(A.F + 6 * N, c) = out[6];
+                put<O>(A.F + 5 * N, c, out[5]);
+                put<O>(A.F + 6 * N, c, out[6]);
             }
 #pragma unroll
             for (int v = 0; v < 5; v++) sm[(8 + v) * NT + tid] = out[v];
@@ -556,7 +549,7 @@ struct BFaceXRows {
         } else {
             const T ra = T(A.rk.a), rb = T(A.rk.b);
 #pragma unroll
-            for (int q = 0; q < 5; q++) at<O>(A.O.f[upd[q]], c) = (uc[q] + ra * (sc[q] - uc[q])) + rb * inc[q];
+            for (int q = 0; q < 5; q++) put<O>(A.O.f[upd[q]], c, (uc[q] + ra * (sc[q] - uc[q])) + rb * inc[q]);
         }
     }
 };
@@ -570,7 +563,7 @@ struct BFaceXRows {
 // Both directions share a launch, the y blocks first: the two are independent,
 // so a small box pays the latency of one march instead of two, and a large one
 // has one ragged end instead of two.
-template <typename T, bool ION, typename O>
+template <typename T, bool ION, class O>
 struct BFaceMarch {
     static constexpr int NT = NTH;
     static constexpr bool XCD = false;
@@ -704,16 +697,17 @@ struct BFaceMarch {
                        R, gm, ION ? gw[1] : gm, ION ? gw[2] : gm, ION, ydx, srl, srr, out);
             srl = srr;
             if (!DIFF) {
-                store_face<O>(F, N, c, out);
+#pragma unroll
+                for (int q = 0; q < 7; q++) put<O>(F + q * N, c, out[q]);
             } else {
+                const int cm = base + (x - 1) * stride;
                 if (x < x1) {
-                    at<O>(F + 5 * N, c) = out[5];
-                    at<O>(F + 6 * N, c) = out[6];
+                    put<O>(F + 5 * N, c, out[5]);
+                    put<O>(F + 6 * N, c, out[6]);
                 }
                 if (x > x0) {
-                    const int cm = base + (x - 1) * stride;
 #pragma unroll
-                    for (int v = 0; v < 5; v++) at<O>(F + v * N, cm) = out[v] - prev[v][tid];
+                    for (int v = 0; v < 5; v++) put<O>(F + v * N, cm, out[v] - prev[v][tid]);
                 }
 #pragma unroll
                 for (int v = 0; v < 5; v++) prev[v][tid] = out[v];
@@ -762,7 +756,7 @@ struct FieldUpdateArgs {
 constexpr int UPD_NT = 256;
 constexpr int UPD_TX = 64;
 
-template <typename T, typename O>
+template <typename T, class O>
 struct BFieldUpdate {
     static constexpr int NT = UPD_NT;
     static constexpr bool XCD = false;
@@ -857,7 +851,7 @@ struct BFieldUpdate {
                 for (int q = 0; q < 3; q++) at<O>(A.O.f[BX + q], c) = inc[q];
             } else {
 #pragma unroll
-                for (int q = 0; q < 3; q++) at<O>(A.O.f[BX + q], c) = (uo[q] + ra * (so[q] - uo[q])) + rb * inc[q];
+                for (int q = 0; q < 3; q++) put<O>(A.O.f[BX + q], c, (uo[q] + ra * (so[q] - uo[q])) + rb * inc[q]);
             }
             Ex_c = Ex_zp;
             Ey_c = Ey_zp;
@@ -1153,7 +1147,7 @@ __device__ __forceinline__ double tail_speed(const StepArgs& a, double rho, doub
 // cells (the upper face of its last cell, also formed by the next segment
 // from the same window) and the update reads one value per field instead of
 // two.
-template <typename T, int NQ, typename O>
+template <typename T, int NQ, class O>
 struct BAdvFaceMarchY {
     static constexpr int NT = NTH;
     static constexpr bool XCD = false;
@@ -1268,7 +1262,7 @@ struct BAdvFaceMarchY {
 #pragma unroll
                 for (int q = 0; q < NQ; q++) {
                     const T d = flux[q] - prev_of(q);
-                    at<O>(A.F + q * N, c) = d;
+                    put<O>(A.F + q * N, c, d);
                 }
             }
 #pragma unroll
@@ -1316,7 +1310,7 @@ struct AdvXZArgs {
     int seg;    // z cells per block
 };
 
-template <typename T, int Q0, int NQ, int MAXT, typename O>
+template <typename T, int Q0, int NQ, int MAXT, class O>
 struct BAdvXZUpdate {
     static constexpr int NT = MAXT;
     static constexpr bool XCD = false;
@@ -1549,7 +1543,7 @@ struct BAdvXZUpdate {
             }
             if (own) {
 #pragma unroll
-                for (int q = 0; q < NQ; q++) at<O>(A.O.f[fld[Q0 + q]], c) = nv[q];
+                for (int q = 0; q < NQ; q++) put<O>(A.O.f[fld[Q0 + q]], c, nv[q]);
                 if (Q0 == 0 && A.dbg) {
                     at<O>(A.O.f[BX], c) = T(0);
                     at<O>(A.O.f[BY], c) = T(0);
@@ -1579,7 +1573,7 @@ struct BAdvXZUpdate {
 // L2; a small box pays the latency of one march instead of two.  (FP64 with the
 // H+ field keeps two launches: the second group's registers leave two waves per
 // SIMD, the first group alone three.)
-template <typename T, int NQ2, int MAXT, typename O>
+template <typename T, int NQ2, int MAXT, class O>
 struct BAdvXZPair {
     using G1 = BAdvXZUpdate<T, 0, 4, MAXT, O>;
     using G2 = BAdvXZUpdate<T, 4, NQ2, MAXT, O>;
@@ -1601,7 +1595,7 @@ struct BAdvXZPair {
 // Tail of the step (after ADV) as a pass of its own: tail_cell on every cell,
 // validity flag, per-block CFL speed maximum.  mode: 1 = full tail, 0 = speed
 // only (state unchanged).
-template <typename T, typename O>
+template <typename T, class O>
 struct BTail {
     static constexpr int NT = NTH;
     static constexpr bool XCD = false;

@@ -86,21 +86,37 @@ __device__ __forceinline__ void decompose(const Geo& g, int c, int& i, int& j, i
     j = row - k * g.ny;
 }
 
-// Value i of an array that starts at a kernel argument (the same address in
-// every lane).  With O = uint32_t the byte offset stays below 2^32 (arrays of
-// at most 4 GiB), so that the load takes the base from scalar registers and one
-// 32-bit offset serves every field of a cell; with 64-bit offsets each access
-// costs a 64-bit vector addition of its own (49 of 1190 instructions of the
-// FP32 x-row kernel).
-// The global address space is stated because the pointers of a multi-box launch
+// How the kernels of a launch reach the fields.  Near: a field is at most 4 GiB,
+// so a value's byte offset is 32 bits wide; the load takes the base from scalar
+// registers and one offset serves every field of a cell (with 64-bit offsets
+// each access costs a 64-bit vector addition of its own, 49 of 1190
+// instructions of the FP32 x-row kernel).  Streamed: the same, and the outputs
+// go past the caches: a box whose arrays exceed the 256 MB Infinity Cache
+// several times over finds nothing of them there in the next kernel, and the
+// stores only evict what neighbouring blocks still read (steps of 256^3 1.2%
+// shorter in FP64 and 2.4% in FP32; of 96^3 FP64 6% longer).  Far: longer
+// fields, streamed.
+struct Near { using Off = uint32_t; static constexpr bool stream = false; };
+struct Streamed { using Off = uint32_t; static constexpr bool stream = true; };
+struct Far { using Off = uint64_t; static constexpr bool stream = true; };
+
+// Value i of an array that starts at the same address in every lane.  The
+// global address space is stated because the pointers of a multi-box launch
 // come from its table in memory, where the compiler would take them for
 // generic ones (flat loads, which also wait for the LDS).
 template <typename T> using Global = __attribute__((address_space(1))) T;
-template <typename O, typename T>
+template <class O, typename T>
 __device__ __forceinline__ Global<T>& at(T* p, int i)
 {
     using C = std::conditional_t<std::is_const<T>::value, const char, char>;
-    return *(Global<T>*)((Global<C>*)p + (O)((O)(unsigned)i * (O)sizeof(T)));
+    using B = typename O::Off;
+    return *(Global<T>*)((Global<C>*)p + (B)((B)(unsigned)i * (B)sizeof(T)));
+}
+template <class O, typename T>
+__device__ __forceinline__ void put(T* p, int i, T v)
+{
+    if constexpr (O::stream) __builtin_nontemporal_store(v, &at<O>(p, i));
+    else at<O>(p, i) = v;
 }
 
 template <typename T> struct Fields { T* f[NF]; };
