@@ -229,6 +229,23 @@ __global__ __launch_bounds__(Body::NT) __attribute__((amdgpu_waves_per_eu(MinWav
 // variables (vn, vt1, vt2, Bt1, Bt2, p) with (n, t1, t2) cyclic from D, its
 // density and its adiabatic index.
 
+// a cell's index as a march walks its line of nd cells from base, periodic: a
+// sum, a comparison and a selection per cell (wrapping the index of every access
+// took some 45 integer instructions per face)
+struct Walk {
+    int c;
+    unsigned stride, base, end;   // end may pass 2^31 in the largest boxes
+    __device__ __forceinline__ Walk(int b, int s, int nd, int x)
+        : c(b + wrapc(x, nd) * s), stride(s), base(b), end((unsigned)b + (unsigned)nd * (unsigned)s)
+    {
+    }
+    __device__ __forceinline__ void next()
+    {
+        const unsigned n = (unsigned)c + stride;
+        c = (int)(n == end ? base : n);
+    }
+};
+
 // the conserved values one cell needs: rho, m (normal, t1, t2), e, both faces
 // of the two transverse fields (c1, c2: the upper neighbours along t1 and t2)
 // and, with the ionisation network, the H2 and H+ densities
@@ -639,9 +656,10 @@ struct BFaceMarch {
         // face x) are loaded one face ahead, so the loads are in flight while
         // the previous face is solved
         Raw<T> nr;
-        auto fetch = [&](int x) {
-            int cn = base + wrapc(x + 2, nd) * stride;
-            raw_load<T, D, ION, O>(A.U, cn, cn + o1, cn + o2, nr);
+        Walk cn(base, stride, nd, x0 + 2);
+        auto fetch = [&]() {
+            raw_load<T, D, ION, O>(A.U, cn.c, cn.c + o1, cn.c + o2, nr);
+            cn.next();
         };
         constexpr bool DIFF = FluxDiff<T>::v;
         const int xe = DIFF ? x1 + 1 : x1;   // faces solved: x0 .. xe - 1
@@ -649,15 +667,19 @@ struct BFaceMarch {
         // sqrt(rho) of the face's left cell, carried (window slot 2 before
         // the first slide is slot 1 of the first face)
         T srl = root_nr(w[6][2]);
-        fetch(x0);
+        fetch();
         // the face's normal field, loaded one face ahead with the entering
         // cell (loaded at the face, its latency stood before the face solve);
         // FP64 with the ionisation network has no registers left for it
         constexpr bool BN_AHEAD = !ION || sizeof(T) == 4;
-        auto bn_of = [&](int x) { return at<O>(A.U.f[BX + D], base + (DIFF ? wrapc(x, nd) : x) * stride); };
-        T bnn = BN_AHEAD ? bn_of(x0) : T(0);
+        // face x is the lower face of cell x, at cf.c (with differences, x = x1
+        // is the upper face of the last cell, periodic); cm: the cell before
+        Walk cf(base, stride, nd, x0);
+        int cm = 0;
+        T bnn = BN_AHEAD ? at<O>(A.U.f[BX + D], cf.c) : T(0);
         auto face = [&](int x) {
-            const T bnx = BN_AHEAD ? bnn : bn_of(x);
+            const int c = cf.c;
+            const T bnx = BN_AHEAD ? bnn : T(at<O>(A.U.f[BX + D], c));
             T qn[6], gn;
             raw_prim<T, ION>(nr, A.a.gamma, qn, gn);
 #pragma unroll
@@ -671,9 +693,10 @@ struct BFaceMarch {
                 for (int m = 0; m < 4; m++) gw[m] = gw[m + 1];
                 gw[4] = gn;
             }
+            cf.next();
             if (x + 1 < xe) {
-                fetch(x + 1);
-                if constexpr (BN_AHEAD) bnn = bn_of(x + 1);
+                fetch();
+                if constexpr (BN_AHEAD) bnn = at<O>(A.U.f[BX + D], cf.c);
             }
             Side<T> R, Ln;
 #pragma unroll
@@ -687,9 +710,6 @@ struct BFaceMarch {
                 dmc[v] = dn;
                 fl[v] = fr;
             }
-            // face x is the lower face of cell x (with differences, x = x1 is
-            // the upper face of the last cell, periodic)
-            int c = base + (DIFF ? wrapc(x, nd) : x) * stride;
             T out[7];
             // left cell x-1 is window slot 1, right cell x is slot 2
             const T srr = root_nr(w[6][2]);
@@ -700,7 +720,6 @@ struct BFaceMarch {
 #pragma unroll
                 for (int q = 0; q < 7; q++) put<O>(F + q * N, c, out[q]);
             } else {
-                const int cm = base + (x - 1) * stride;
                 if (x < x1) {
                     put<O>(F + 5 * N, c, out[5]);
                     put<O>(F + 6 * N, c, out[6]);
@@ -711,6 +730,7 @@ struct BFaceMarch {
                 }
 #pragma unroll
                 for (int v = 0; v < 5; v++) prev[v][tid] = out[v];
+                cm = c;
             }
             L = Ln;
         };
@@ -1209,12 +1229,13 @@ struct BAdvFaceMarchY {
         T rsl = rsqrt_nr(w[0][2]);
         // the cell entering the window, loaded one face ahead
         T nw[NQ];
-        auto fetch = [&](int x) {
-            int cn = base + wrapc(x + 2, nd) * stride;
+        Walk cn(base, stride, nd, x0 + 2);
+        auto fetch = [&]() {
 #pragma unroll
-            for (int q = 0; q < NQ; q++) nw[q] = at<O>(A.U.f[fld[q]], cn);
+            for (int q = 0; q < NQ; q++) nw[q] = at<O>(A.U.f[fld[q]], cn.c);
+            cn.next();
         };
-        fetch(x0);
+        fetch();
         // the flux of the lower face of the cell before x: in registers, or
         // in the thread's own LDS slots where registers would not leave two
         // waves per SIMD (FP64 with the H+ field)
@@ -1222,14 +1243,15 @@ struct BAdvFaceMarchY {
         __shared__ T prev_lds[PREV_LDS ? NQ * NT : 1];
         T prev[PREV_LDS ? 1 : NQ];
         auto prev_of = [&](int q) -> T { return PREV_LDS ? prev_lds[q * NT + tid] : prev[q]; };
-        for (int x = x0; x <= x1; x++) {
+        int c = base + (x0 - 1) * stride;   // the cell before face x
+        for (int x = x0; x <= x1; x++, c += stride) {
 #pragma unroll
             for (int q = 0; q < NQ; q++) {
 #pragma unroll
                 for (int m = 0; m < 4; m++) w[q][m] = w[q][m + 1];
                 w[q][4] = nw[q];
             }
-            if (x < x1) fetch(x + 1);
+            if (x < x1) fetch();
             // sqrt(rho)-weighted face velocity from cells x-1 (slot 1) and x
             // (slot 2); sqrt(rho) v = m / sqrt(rho), m_y is field 2
             const T rsr = rsqrt_nr(w[0][2]);
@@ -1258,7 +1280,6 @@ struct BAdvFaceMarchY {
             }
             if (x > x0) {
                 // cell x - 1: its upper face is face x
-                const int c = base + (x - 1) * stride;
 #pragma unroll
                 for (int q = 0; q < NQ; q++) {
                     const T d = flux[q] - prev_of(q);
