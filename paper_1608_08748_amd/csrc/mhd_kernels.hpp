@@ -333,14 +333,16 @@ __device__ __forceinline__ void check_dt(const FaceArgs<T>& A, int blk, int tid)
 template <typename T> struct FluxDiff { static constexpr bool v = sizeof(T) == 4; };
 
 // NONADV faces along x with row segments per block (RowTile), fused with the
-// update of m, E and e.  Each thread owns one cell, forms its primitives and computes,
-// once each, its limited slopes, the interface values at its lower face and
-// its parabolas (Sec. 2.1); neighbours' primitives, slopes, interface values
-// and parabola sides come through LDS.  After
-// the face solve the row's x-face fluxes are exchanged the same way, so the
-// thread forms the flux differences of its cell (y and z faces from the face
-// kernels that ran before), the p dV work, the gravity sources and the
-// Runge-Kutta combination of m, E, e (Sec. 2.2).  Only the edge-field
+// update of m, E and e.  Each thread owns one cell, forms its primitives and
+// computes, once each, its limited slopes, the interface values at its lower
+// face and its parabolas (Sec. 2.1); neighbours' primitives, slopes, interface
+// values and parabola sides come through LDS.  After the face solve the
+// segment's x-face fluxes are exchanged the same way, so the thread forms the
+// flux differences of its cell (y and z faces from the face kernels that ran
+// before), the p dV work, the gravity sources and the Runge-Kutta combination
+// of m, E, e (Sec. 2.2).  At 256^3 it moves 31 values per cell, 4.2 GB in FP64
+// at 4.9 TB/s (FP32 5.6 TB/s) with the VALU 60% busy: 870 -> 842 us a launch,
+// FP32 392 -> 371, by dt constants, 32-bit offsets and streamed outputs.  Only the edge-field
 // components of the x faces are stored, for the face-field update.  Dynamic
 // LDS: XROW_SLOTS x NT values, value k of thread t at k * NT + t: primitives
 // in slots 0-7 with sqrt(rho) in 14, slopes 8-13, the two edge values of each
@@ -579,7 +581,12 @@ struct BFaceXRows {
 // face of its segment's last cell; the previous face's fluxes wait in LDS.
 // Both directions share a launch, the y blocks first: the two are independent,
 // so a small box pays the latency of one march instead of two, and a large one
-// has one ragged end instead of two.
+// has one ragged end instead of two (32^3 FP64 18.4 -> 10 us, 256^3 1124 ->
+// 1100).  At 256^3 FP64 the VALU is 89% busy at the clock the kernel runs at
+// (1.9 GHz), 30 values per cell and 1.27 ms became 1.12 with the parabola's
+// early tests, FP32 0.67 -> 0.55 ms with them, the median slopes and the walked
+// indices; there three waves per SIMD leave a third of the issue slots unused
+// (a fourth needs 128 registers: spills, twice the time).
 template <typename T, bool ION, class O>
 struct BFaceMarch {
     static constexpr int NT = NTH;
@@ -636,8 +643,7 @@ struct BFaceMarch {
         // parabolas of cell x0 - 1 (the left side of the first face).  Along
         // the march each cell's limited slope and each face's interface value
         // is computed once and carried: dmc = slope of the current cell,
-        // fl = interface value at its lower face (Step 1, the same calls as
-        // in parabola())
+        // fl = interface value at its lower face (Step 1)
         Side<T> L;
         T dmc[6], fl[6];
 #pragma unroll
@@ -757,6 +763,8 @@ struct BFaceMarch {
 // along z over a segment of cells (ZTile); the Ex, Ey on the upper z edges of
 // cell k and the edge-field components they read are the lower ones of cell
 // k+1, so they are carried instead of read or formed again (same arithmetic).
+// Bound by memory: 15 values per cell, 399 us at 256^3 FP64 (5.0 TB/s), FP32
+// 210 (220 before 32-bit offsets and streamed outputs).
 template <typename T>
 struct FieldUpdateArgs {
     Geo g;
@@ -1309,8 +1317,10 @@ struct BAdvFaceMarchY {
 // through memory; the y difference comes from memory (stored by the y march).
 // The fields are split over two launches so that a thread holds a small window
 // and more waves fit on a SIMD; both read rho and the momenta of the faces for
-// the face velocities.  Three block barriers per plane (values, slopes,
-// fluxes); the LDS is double-buffered by plane parity, so a buffer is
+// the face velocities.  At 256^3 FP64 the two groups take 0.97 ms (1.13 before
+// the parabola's early tests and the shared launch), FP32 0.47 (0.60): 31 values
+// per cell at 4.3 TB/s, the VALU 73% busy.  Three block barriers per plane
+// (values, slopes, fluxes; two were level); the LDS is double-buffered by plane parity, so a buffer is
 // rewritten only after every thread has passed the barriers that follow its
 // last reads.  Dynamic LDS: 2 x (NV + 2 NQ) x NT values.  Threads beyond the
 // block's segments (and the segments of a last, partial group) reach every
@@ -1614,8 +1624,10 @@ struct BAdvXZPair {
 // ---------------------------------------------------------------- tail and reductions
 
 // Tail of the step (after ADV) as a pass of its own: tail_cell on every cell,
-// validity flag, per-block CFL speed maximum.  mode: 1 = full tail, 0 = speed
-// only (state unchanged).
+// validity flag, per-block CFL speed maximum.  12 values per cell: 279 us at
+// 256^3 FP64, 5.8 TB/s (381 us when its divisions and exponentials bound it),
+// FP32 233 us (377).
+// mode: 1 = full tail, 0 = speed only (state unchanged).
 template <typename T, class O>
 struct BTail {
     static constexpr int NT = NTH;
