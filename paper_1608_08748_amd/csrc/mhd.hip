@@ -810,20 +810,21 @@ void emit_poisson(mhd_box* b, Emit& e)
     const size_t xshm = (size_t)fa.lpb * g.nx * sizeof(Cx<T>);
     e.template launch<BFftX<T, 0>>(MHD_K_POISSON, xb, xshm, fa);
     // y and z passes: tx columns of a line set, tx x (n + 1) complex in LDS
-    auto tx_of = [&](int n) {
-        int t = FFT_YZ_VALUES / n;
-        t = t < 1 ? 1 : t;
-        return t > g.nx ? g.nx : t;
+    // (powers of two, like the axes)
+    auto pass = [&](int n) {
+        const int t = std::min(FFT_YZ_VALUES / n, g.nx);
+        fa.logt = ilog2(t);
+        return t;
     };
-    fa.tx = tx_of(g.ny);
-    e.template launch<BFftYZ<T, 1, 0>>(MHD_K_POISSON, ((g.nx + fa.tx - 1) / fa.tx) * g.nz,
-                                       (size_t)fa.tx * (g.ny + 1) * sizeof(Cx<T>), fa);
-    fa.tx = tx_of(g.nz);
-    e.template launch<BFftYZ<T, 2, 2>>(MHD_K_POISSON, ((g.nx + fa.tx - 1) / fa.tx) * g.ny,
-                                       (size_t)fa.tx * (g.nz + 1) * sizeof(Cx<T>), fa);
-    fa.tx = tx_of(g.ny);
-    e.template launch<BFftYZ<T, 1, 1>>(MHD_K_POISSON, ((g.nx + fa.tx - 1) / fa.tx) * g.nz,
-                                       (size_t)fa.tx * (g.ny + 1) * sizeof(Cx<T>), fa);
+    int tx = pass(g.ny);
+    e.template launch<BFftYZ<T, 1, 0>>(MHD_K_POISSON, (g.nx / tx) * g.nz,
+                                       (size_t)tx * (g.ny + 1) * sizeof(Cx<T>), fa);
+    tx = pass(g.nz);
+    e.template launch<BFftYZ<T, 2, 2>>(MHD_K_POISSON, (g.nx / tx) * g.ny,
+                                       (size_t)tx * (g.nz + 1) * sizeof(Cx<T>), fa);
+    tx = pass(g.ny);
+    e.template launch<BFftYZ<T, 1, 1>>(MHD_K_POISSON, (g.nx / tx) * g.nz,
+                                       (size_t)tx * (g.ny + 1) * sizeof(Cx<T>), fa);
     e.template launch<BFftX<T, 1>>(MHD_K_POISSON, xb, xshm, fa);
 }
 

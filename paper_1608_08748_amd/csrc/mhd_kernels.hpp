@@ -1005,12 +1005,13 @@ struct FftArgs {
     double gscale;            // -(2/3) pi G h^2 / N (Green's numerator with the 1/N of the inverse)
     int logn[3];
     int lpb;                  // x lines per block
-    int tx;                   // x columns per block of the y/z passes
+    int logt;                 // log2 of the x columns per block of the y/z passes
 };
 
 // Transforms along x: INV = 0 reads the density and writes its transform to
-// Z; INV = 1 inverts Z and writes the real part, the potential.  Dynamic LDS:
-// lpb x nx complex values.
+// Z; INV = 1 inverts Z and writes the real part, the potential.  A thread's
+// loads are all issued before the first is stored to LDS: a loop of load and
+// store waits for memory once per value.  Dynamic LDS: lpb x nx complex values.
 template <typename T, int INV>
 struct BFftX {
     static constexpr int NT = NTH;
@@ -1023,27 +1024,32 @@ struct BFftX {
         Cx<T>* a = reinterpret_cast<Cx<T>*>(smem_raw);
         const int lines = A.g.ny * A.g.nz;
         const int l0 = blk * A.lpb;
-        for (int t = tid; t < A.lpb * n; t += NT) {
+        constexpr int PER = FFT_X_VALUES / NT;
+        Cx<T> v[PER];
+#pragma unroll
+        for (int u = 0; u < PER; u++) {
+            const int t = tid + u * NT;
             const int line = l0 + (t >> logn);
-            T re = T(0), im = T(0);
-            if (line < lines) {
+            v[u] = { T(0), T(0) };
+            if (t < A.lpb * n && line < lines) {
                 const size_t c = (size_t)line * n + (t & (n - 1));
-                if (INV) {
-                    re = A.Z[c].re;
-                    im = A.Z[c].im;
-                } else {
-                    re = A.rho[c];
-                }
+                if (INV) v[u] = A.Z[c];
+                else v[u].re = A.rho[c];
             }
-            a[t].re = re;
-            a[t].im = im;
+        }
+#pragma unroll
+        for (int u = 0; u < PER; u++) {
+            const int t = tid + u * NT;
+            if (t < A.lpb * n) a[t] = v[u];
         }
         __syncthreads();
         stockham<T, FFT_X_VALUES>(a, logn, A.lpb, n, A.tw[0], INV != 0, tid, NT);
         const Cx<T>* r = a;
-        for (int t = tid; t < A.lpb * n; t += NT) {
+#pragma unroll
+        for (int u = 0; u < PER; u++) {
+            const int t = tid + u * NT;
             const int line = l0 + (t >> logn);
-            if (line >= lines) continue;
+            if (t >= A.lpb * n || line >= lines) continue;
             const size_t c = (size_t)line * n + (t & (n - 1));
             if (INV) A.phi[c] = r[t].re;
             else A.Z[c] = r[t];
@@ -1054,8 +1060,12 @@ struct BFftX {
 // Transforms along D = y or z of tx adjacent x columns per block (row
 // segments of tx values are read and written together).  MODE 0: forward;
 // 1: inverse; 2 (D = z): forward, multiply by the Green's function of the
-// 27-point stencil, inverse.  Dynamic LDS: tx x (n + 1) complex values (a
-// padded line stride).
+// 27-point stencil, inverse.  A pass moves 537 MB at 256^3 FP64, 114 us at a
+// copy's rate: 129 (inverse), 146 (forward) and 263 us (mode 2, two transforms
+// between its loads and stores) against 149, 176 and 274 as loops of one load
+// and one store to LDS, each of which waits for memory.  Real and imaginary
+// parts are held apart: an array of pairs went to scratch (250 us).  Dynamic
+// LDS: tx x (n + 1) complex values (a padded line stride).
 template <typename T, int D, int MODE>
 struct BFftYZ {
     static constexpr int NT = NTH;
@@ -1066,22 +1076,30 @@ struct BFftYZ {
         extern __shared__ unsigned char smem_raw[];
         const Geo& g = A.g;
         const int n = D == 1 ? g.ny : g.nz, logn = A.logn[D];
-        const int tx = A.tx, ls = n + 1;
+        const int logt = A.logt, tx = 1 << logt, ls = n + 1;
         Cx<T>* a = reinterpret_cast<Cx<T>*>(smem_raw);
-        const int ntx = (g.nx + tx - 1) / tx;
-        const int x0 = (blk % ntx) * tx;
-        const int o = blk / ntx;   // z index (D = y) or y index (D = z)
+        const int logb = A.logn[0] - logt;   // blocks per row
+        const int x0 = (blk & ((1 << logb) - 1)) << logt;
+        const int o = blk >> logb;           // z index (D = y) or y index (D = z)
         const size_t stride = D == 1 ? (size_t)g.nx : (size_t)g.nxy;
         const size_t base = (size_t)x0 + (D == 1 ? (size_t)o * g.nxy : (size_t)o * g.nx);
-        for (int t = tid; t < tx * n; t += NT) {
-            const int p = t / tx, c = t - p * tx;
-            T re = T(0), im = T(0);
-            if (x0 + c < g.nx) {
-                re = A.Z[base + p * stride + c].re;
-                im = A.Z[base + p * stride + c].im;
+        constexpr int PER = FFT_YZ_VALUES / NT;
+        T re[PER], im[PER];
+#pragma unroll
+        for (int u = 0; u < PER; u++) {
+            const int t = tid + u * NT;
+            const size_t c = base + (t < tx * n ? (t >> logt) * stride + (t & (tx - 1)) : 0);
+            re[u] = A.Z[c].re;
+            im[u] = A.Z[c].im;
+        }
+#pragma unroll
+        for (int u = 0; u < PER; u++) {
+            const int t = tid + u * NT;
+            Cx<T>& w = a[(t & (tx - 1)) * ls + (t >> logt)];
+            if (t < tx * n) {
+                w.re = re[u];
+                w.im = im[u];
             }
-            a[c * ls + p].re = re;
-            a[c * ls + p].im = im;
         }
         __syncthreads();
         stockham<T, FFT_YZ_VALUES>(a, logn, tx, ls, A.tw[D], MODE == 1, tid, NT);
@@ -1089,10 +1107,12 @@ struct BFftYZ {
         if (MODE == 2) {
             // mode (kx, ky, kz) = (x0 + c, o, p); the zero mode (the mean
             // density of the periodic box) has no potential
-            for (int t = tid; t < tx * n; t += NT) {
-                const int c = t / n, p = t - c * n;
+#pragma unroll
+            for (int u = 0; u < PER; u++) {
+                const int t = tid + u * NT;
+                if (t >= tx * n) continue;
+                const int c = t >> logn, p = t & (n - 1);
                 const int kx = x0 + c;
-                if (kx >= g.nx) continue;
                 double f = 0.0;
                 if (kx != 0 || o != 0 || p != 0)
                     f = A.gscale / (1.0 - A.sf[0][kx] * A.sf[1][o] * A.sf[2][p]);
@@ -1103,9 +1123,11 @@ struct BFftYZ {
             __syncthreads();
             stockham<T, FFT_YZ_VALUES>(a, logn, tx, ls, A.tw[D], true, tid, NT);
         }
-        for (int t = tid; t < tx * n; t += NT) {
-            const int p = t / tx, c = t - p * tx;
-            if (x0 + c < g.nx) A.Z[base + p * stride + c] = r[c * ls + p];
+#pragma unroll
+        for (int u = 0; u < PER; u++) {
+            const int t = tid + u * NT;
+            const int p = t >> logt, c = t & (tx - 1);
+            if (t < tx * n) A.Z[base + p * stride + c] = r[c * ls + p];
         }
     }
 };
