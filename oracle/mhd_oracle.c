@@ -385,6 +385,16 @@ double orc_gamma_cell(const orc_params *P, double rho, double h2, double hp)
     return (5.0 * nH + 5.0 * ne + 7.0 * nH2) / (3.0 * nH + 3.0 * ne + 5.0 * nH2);
 }
 
+/* atomic hydrogen of a cell, rho - rho_H2 - rho_H+: the chemistry's quotients
+ * by n_u can leave the other two a unit in the last place above rho in a cell
+ * that is all molecular or ionised; a negative remainder counts as none (the
+ * cooling takes a power of it) */
+static double atomic_h(double rho, double h2, double hp)
+{
+    double a = rho - h2 - hp;
+    return a < 0.0 ? 0.0 : a;
+}
+
 /* mean particle mass in m_H: rho / (n_H + n_H2 + n_H+ + n_e) per unit n_u */
 static double mean_mass(double rho, double h2, double hp)
 {
@@ -755,7 +765,7 @@ double orc_chem_cell(const orc_params *P, double rho, double e, double h2, doubl
     double xh2 = h2 / rho;
     double mu = 1.0 / (1.0 - 0.5 * xh2);
     double T = P->T_unit * mu * p / rho;
-    double nH = P->n_unit * (rho - h2);
+    double nH = P->n_unit * atomic_h(rho, h2, 0.0);
     double nH2 = P->n_unit * h2 / 2.0;
     double n = nH + nH2;
     double k1b = orc_k1_base(T), k2 = orc_k2(T), k3 = orc_k3(T), k4 = orc_k4();
@@ -827,7 +837,7 @@ double orc_heat_cool(const orc_params *P, double rho, double e, double h2, doubl
     double p = (P->gamma - 1.0) * e;
     double mu = 1.0 / (1.0 - 0.5 * (h2 / rho));
     double T = P->T_unit * mu * p / rho;
-    double nH = P->n_unit * (rho - h2);
+    double nH = P->n_unit * atomic_h(rho, h2, 0.0);
     double nH2 = P->n_unit * h2 / 2.0;
     double n = nH + nH2;
     /* Gamma1: 7.2e-12 erg per H2 formed, times the formation rate C of
@@ -861,7 +871,7 @@ double orc_heat_cool_ion(const orc_params *P, double rho, double e, double h2, d
     double gam = orc_gamma_cell(P, rho, h2, hp);
     double p = (gam - 1.0) * e;
     double T = P->T_unit * mean_mass(rho, h2, hp) * p / rho;
-    double nH = P->n_unit * (rho - h2 - hp);
+    double nH = P->n_unit * atomic_h(rho, h2, hp);
     double nH2 = P->n_unit * h2 / 2.0;
     double ne = P->n_unit * hp;
     double n = nH + nH2 + ne;
@@ -1058,7 +1068,7 @@ void orc_chem_cell_ion(const orc_params *P, double rho, double e, double h2, dou
     double gam = orc_gamma_cell(P, rho, h2, hp);
     double p = (gam - 1.0) * e;
     double T = P->T_unit * mean_mass(rho, h2, hp) * p / rho;
-    double nH = P->n_unit * (rho - h2 - hp);
+    double nH = P->n_unit * atomic_h(rho, h2, hp);
     double nH2 = P->n_unit * h2 / 2.0;
     double ne = P->n_unit * hp;
     double n = nH + nH2 + ne;

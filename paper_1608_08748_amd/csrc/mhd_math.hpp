@@ -451,7 +451,10 @@ constexpr double LN10 = 2.302585092994045684;
 constexpr double INV_LN10 = 0.43429448190325182765;
 
 // number densities (cm^-3) and temperature of a cell: n_H = n_u (rho - h2 -
-// hp), T = T_u mu p / rho with the mean mass mu = 1 / (1 - x_H2/2 + x_H+)
+// hp), T = T_u mu p / rho with the mean mass mu = 1 / (1 - x_H2/2 + x_H+).  In a
+// cell whose hydrogen is all molecular or ionised the chemistry's quotients by
+// n_u can leave h2 + hp a unit in the last place above rho; the cooling takes a
+// power of n_H, so a negative remainder counts as none.
 struct Gas {
     double nH, nH2, ne, n, T, iT;
 };
@@ -459,7 +462,8 @@ struct Gas {
 __device__ __forceinline__ Gas gas_state(const ChemArgs& ch, double gamma, double rho, double e, double h2, double hp)
 {
     Gas g;
-    g.nH = ch.n_unit * (rho - h2 - hp);
+    const double atomic = rho - h2 - hp;
+    g.nH = ch.n_unit * (atomic < 0.0 ? 0.0 : atomic);
     g.nH2 = ch.n_unit * h2 / 2.0;
     g.ne = ch.n_unit * hp;
     g.n = g.nH + g.nH2 + g.ne;
