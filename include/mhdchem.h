@@ -330,7 +330,8 @@ int mhd_server_submit(mhd_server *s, const mhd_request *r, const double *prim, u
  * calling while requests are outstanding).  A finished box's memory returns to
  * the pool when its last step is launched (with keep_state, once its state is
  * copied out).  Outputs the numbers of boxes still stepping and of queued
- * requests. */
+ * requests.  MHD_ENOMEM if there is no host memory for a finished box's kept
+ * state: nothing is lost, the next call reports the box. */
 int mhd_server_progress(mhd_server *s, int *n_active, int *n_pending);
 
 /* Take up to cap completion records (oldest first). */

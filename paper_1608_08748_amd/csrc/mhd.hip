@@ -27,6 +27,7 @@
 #include <cstdint>
 #include <cstring>
 #include <deque>
+#include <list>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -1314,13 +1315,17 @@ struct mhd_server {
     double t0;
     std::vector<MultiRec> recs;
     // pipelined rounds: a call launches its round and then waits for the one
-    // before; the boxes that finished in the last launched round have their
-    // totals and flags on the way to pinned slots (slot k of the round's half)
-    struct Retiring {
+    // before.  A box is in exactly one of: active, retiring (by the half of the
+    // round that finishes it; its totals and flags are on the way to the pinned
+    // slot of its place in the list), finished (round over, totals and flags at
+    // hand, not reported yet: the report needs host memory and is tried again by
+    // the next call if there is none)
+    struct Finished {
         Active a;
-        int slot;
+        double totals[NF];
+        uint32_t flags;
     };
-    std::vector<Retiring> retiring;
+    std::list<Finished> retiring[2], finished;
     hipEvent_t ev[2];
     int ev_ready;
     int64_t rounds;        // rounds launched
@@ -1511,14 +1516,11 @@ double* ret_slot(mhd_server* sv, int half, int k)
                                      ((size_t)half * SERVER_MAX_SLOTS + k) * SERVER_RET_BYTES);
 }
 
-// completion record of a box whose last round has finished (its totals and
-// flags are in its return slot)
-int server_retire(mhd_server* sv, mhd_server::Retiring& r, int half)
+// reports a finished box: its completion record and, where it was asked for,
+// its state.  On a failure nothing has changed.
+int server_report(mhd_server* sv, const mhd_server::Finished& f)
 {
-    mhd_server::Active& a = r.a;
-    const double* slot = ret_slot(sv, half, r.slot);
-    uint32_t fl;
-    memcpy(&fl, slot + NF, sizeof(fl));
+    const mhd_server::Active& a = f.a;
     mhd_completion c;
     memset(&c, 0, sizeof(c));
     c.id = a.id;
@@ -1527,21 +1529,31 @@ int server_retire(mhd_server* sv, mhd_server::Retiring& r, int half)
     c.t_admit = a.t_admit;
     c.cells = (int64_t)a.box->g.n;
     c.bytes = a.bytes;
-    memcpy(c.totals, slot, NF * sizeof(double));
-    int s2 = (fl & 1u) ? MHD_ENONPHYS : (fl & 2u) ? MHD_ECFL : MHD_OK;
-    c.status = s2;
+    memcpy(c.totals, f.totals, sizeof(f.totals));
+    c.status = flags_status(f.flags);
+    HostState buf;
     if (a.keep) {
         // the kept state is copied out before the box's memory is released
-        HostState buf;
         if (!buf.resize((size_t)NF * a.box->g.n)) return MHD_ENOMEM;
-        int s3 = sv->p.precision == MHD_FP64 ? get_f64<double>(a.box, sv->ring, buf.v.get())
-                                             : get_f64<float>(a.box, sv->ring, buf.v.get());
-        if (s3 == MHD_OK || s3 == s2) std::swap(sv->results[a.id], buf);
-        else if (s3 == MHD_EDEVICE || s3 == MHD_ENOMEM) return s3;
-        pool_free(sv, a.off, a.bytes);
+        const int st = sv->p.precision == MHD_FP64 ? get_f64<double>(a.box, sv->ring, buf.v.get())
+                                                   : get_f64<float>(a.box, sv->ring, buf.v.get());
+        if (st != MHD_OK && st != c.status) return st;
     }
     c.t_done = now_s() - sv->t0;
-    sv->done.push_back(c);
+    try {
+        sv->done.push_back(c);
+    } catch (const std::bad_alloc&) {
+        return MHD_ENOMEM;
+    }
+    if (a.keep) {
+        try {
+            std::swap(sv->results[a.id], buf);
+        } catch (const std::bad_alloc&) {
+            sv->done.pop_back();
+            return MHD_ENOMEM;
+        }
+        pool_free(sv, a.off, a.bytes);
+    }
     delete a.box;
     return MHD_OK;
 }
@@ -1550,52 +1562,69 @@ int server_progress(mhd_server* sv, int* nact, int* npend)
 {
     int st = server_admit(sv);
     if (st) return st;
-    std::vector<mhd_server::Retiring> now_ret;
     const int half = (int)(sv->rounds & 1);
     bool launched = false;
     if (!sv->active.empty()) {
+        std::list<mhd_server::Finished> last;   // the boxes that this round finishes
+        try {
+            for (const mhd_server::Active& a : sv->active)
+                if (a.done + 1 >= a.steps) last.emplace_back();
+        } catch (const std::bad_alloc&) {
+            return MHD_ENOMEM;
+        }
         st = sv->p.precision == MHD_FP64 ? server_round<double>(sv, half) : server_round<float>(sv, half);
         if (st) return st;
         // boxes that have run their steps leave the round: their totals and
         // flags go to pinned slots behind the round on the stream, and (unless
         // their state is kept) their memory returns to the pool at once, since
         // anything that reuses it is queued behind
-        std::vector<mhd_server::Active> keep;
+        int k = 0;
         for (mhd_server::Active& a : sv->active) {
-            a.done++;
-            if (a.done < a.steps) {
-                keep.push_back(a);
-                continue;
-            }
-            const int k = (int)now_ret.size();
-            double* slot = ret_slot(sv, half, k);
+            if (a.done + 1 < a.steps) continue;
+            double* slot = ret_slot(sv, half, k++);
             int s2 = sv->p.precision == MHD_FP64 ? totals_launch<double>(a.box) : totals_launch<float>(a.box);
             if (s2 ||
                 hipMemcpyAsync(slot, a.box->tot_dev, NF * sizeof(double), hipMemcpyDeviceToHost, sv->s) != hipSuccess ||
                 hipMemcpyAsync(slot + NF, a.box->flags, sizeof(uint32_t), hipMemcpyDeviceToHost, sv->s) != hipSuccess)
                 return MHD_EDEVICE;
-            now_ret.push_back({ a, k });
+        }
+        if (hipEventRecord(sv->ev[half], sv->s) != hipSuccess) return MHD_EDEVICE;
+        size_t stay = 0;
+        auto f = last.begin();
+        for (mhd_server::Active& a : sv->active) {
+            if (++a.done < a.steps) {
+                sv->active[stay++] = a;
+                continue;
+            }
+            (f++)->a = a;
             if (!a.keep) pool_free(sv, a.off, a.bytes);
         }
-        sv->active.swap(keep);
-        if (hipEventRecord(sv->ev[half], sv->s) != hipSuccess) return MHD_EDEVICE;
+        sv->active.resize(stay);
+        sv->retiring[half].swap(last);
         sv->rounds++;
         launched = true;
     }
-    // the previous round: wait for it and report the boxes that finished in it
+    if (nact) *nact = (int)sv->active.size();
+    if (npend) *npend = (int)sv->pending.size();
+    // the previous round: wait for it and take its boxes' totals and flags (the
+    // slots are written again by the round after the one just launched)
     if (sv->prev_launched) {
         const int ph = half ^ 1;   // round rounds - 1 (launched by the previous call)
         if (hipEventSynchronize(sv->ev[ph]) != hipSuccess) return MHD_EDEVICE;
-        for (mhd_server::Retiring& r : sv->retiring) {
-            st = server_retire(sv, r, ph);
-            if (st) return st;
+        int k = 0;
+        for (mhd_server::Finished& f : sv->retiring[ph]) {
+            const double* slot = ret_slot(sv, ph, k++);
+            memcpy(f.totals, slot, sizeof(f.totals));
+            memcpy(&f.flags, slot + NF, sizeof(f.flags));
         }
-        sv->retiring.clear();
+        sv->finished.splice(sv->finished.end(), sv->retiring[ph]);
     }
-    sv->retiring.swap(now_ret);
     sv->prev_launched = launched;
-    if (nact) *nact = (int)sv->active.size();
-    if (npend) *npend = (int)sv->pending.size();
+    while (!sv->finished.empty()) {
+        st = server_report(sv, sv->finished.front());
+        if (st) return st;
+        sv->finished.pop_front();
+    }
     return MHD_OK;
 }
 
@@ -1930,7 +1959,8 @@ int mhd_server_destroy(mhd_server* sv)
     if (!sv) return MHD_OK;
     (void)hipStreamSynchronize(sv->s);
     for (mhd_server::Active& a : sv->active) delete a.box;
-    for (mhd_server::Retiring& r : sv->retiring) delete r.a.box;
+    for (const std::list<mhd_server::Finished>* l : { &sv->retiring[0], &sv->retiring[1], &sv->finished })
+        for (const mhd_server::Finished& f : *l) delete f.a.box;
     if (sv->ev_ready) {
         (void)hipEventDestroy(sv->ev[0]);
         (void)hipEventDestroy(sv->ev[1]);

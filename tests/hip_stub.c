@@ -1,0 +1,51 @@
+/* The HIP calls of libmhdchem.so on the CPU, for tests of its host code: "device"
+ * memory is host memory, copies are memcpy, kernels do nothing.  Loaded globally
+ * before the library, so that its symbols come first.  The switches make a call
+ * fail as a test asks for. */
+#include <stdlib.h>
+#include <string.h>
+
+typedef struct { unsigned x, y, z; } dim3_t;
+
+int stub_fail_new;        /* let the n-th array allocation of stub_new_bytes from now on fail (0: none) */
+size_t stub_new_bytes;
+
+/* operator new[](size_t, nothrow) */
+void *_ZnamRKSt9nothrow_t(size_t n, const void *tag)
+{
+    (void)tag;
+    if (stub_fail_new && n == stub_new_bytes && --stub_fail_new == 0) return 0;
+    return malloc(n);
+}
+
+void **__hipRegisterFatBinary(const void *d) { static void *h; (void)d; return &h; }
+void __hipRegisterFunction(void) {}
+void __hipRegisterVar(void) {}
+void __hipUnregisterFatBinary(void) {}
+int __hipPushCallConfiguration(dim3_t g, dim3_t b, size_t shm, void *s) { (void)g; (void)b; (void)shm; (void)s; return 0; }
+int __hipPopCallConfiguration(dim3_t *g, dim3_t *b, size_t *shm, void **s)
+{
+    memset(g, 0, sizeof(*g));
+    memset(b, 0, sizeof(*b));
+    *shm = 0;
+    *s = 0;
+    return 0;
+}
+int hipLaunchKernel(void) { return 0; }
+int hipFuncSetAttribute(void) { return 0; }
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipDeviceGetAttribute(int *v, int a, int d) { (void)a; (void)d; *v = 256; return 0; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *v) { *v = 1; return 0; }
+int hipGetLastError(void) { return 0; }
+int hipStreamSynchronize(void *s) { (void)s; return 0; }
+int hipEventCreate(void **e) { *e = malloc(1); return 0; }
+int hipEventCreateWithFlags(void **e, unsigned f) { (void)f; *e = malloc(1); return 0; }
+int hipEventDestroy(void *e) { free(e); return 0; }
+int hipEventRecord(void *e, void *s) { (void)e; (void)s; return 0; }
+int hipEventSynchronize(void *e) { (void)e; return 0; }
+int hipEventElapsedTime(float *ms) { *ms = 0; return 0; }
+int hipHostMalloc(void **p, size_t n, unsigned f) { (void)f; *p = malloc(n); return 0; }
+int hipHostFree(void *p) { free(p); return 0; }
+int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *st) { (void)k; (void)st; memcpy(d, s, n); return 0; }
+int hipGetSymbolAddress(void **p) { *p = 0; return 1; }
+int hipPointerGetAttributes(void *a, const void *p) { (void)p; memset(a, 0, 32); return 0; }
