@@ -1646,9 +1646,9 @@ struct BAdvXZPair {
 // ---------------------------------------------------------------- tail and reductions
 
 // Tail of the step (after ADV) as a pass of its own: tail_cell on every cell,
-// validity flag, per-block CFL speed maximum.  12 values per cell: 279 us at
-// 256^3 FP64, 5.8 TB/s (381 us when its divisions and exponentials bound it),
-// FP32 233 us (377).
+// validity flag, per-block CFL speed maximum.  12 values per cell: 281 us at
+// 256^3 FP64, 5.7 TB/s (381 us when its divisions and exponentials bound it),
+// FP32 238 us (377).
 // mode: 1 = full tail, 0 = speed only (state unchanged).
 template <typename T, class O>
 struct BTail {
