@@ -569,7 +569,9 @@ __device__ __forceinline__ double heat_cool(int ion, const Gas& g)
     const double lh2 = hoth ? 3.9e-19 * exp(-6118.0 * g.iT) : exp10(-19.24 + 0.474 * x - 1.247 * x * x);
     const double fl2 = hotl ? 1.38e-22 * exp(-9243.0 * g.iT) : exp10(-22.9 - 0.553 * x - 1.148 * x * x);
     const double ll2 = (pow(g.nH2, 0.77) + 1.2 * pow(g.nH, 0.77)) * fl2;
-    const double l2 = quot(g.nH2 * (lh2 * ll2), lh2 + ll2);   // n_H2 L_H / (1 + L_H / L_L)
+    // n_H2 L_H / (1 + L_H / L_L); both limits underflow in the coldest gas, and
+    // the reciprocal of a sum below the normal range is infinite
+    const double l2 = quot(g.nH2 * (lh2 * ll2), lh2 + ll2 + 1e-300);
     const double a = 1.0 + ikb_ev * g.iT;
     const double a45 = 1.0 + 1.0 / (8.617333262e-5 * 4500.0);
     const double lnf = 0.5 * lnT + log(a * g.n) - a;   // with the log(n) of the limit

@@ -73,3 +73,26 @@ def test_cooling_of_cold_gas():
     rel = np.concatenate(rel)
     print("cooling: rms %.2e max %.2e of %d cells" % (np.sqrt((rel ** 2).mean()), np.abs(rel).max(), len(rel)))
     assert np.sqrt((rel ** 2).mean()) <= 6e-15
+
+
+def test_cooling_where_the_limits_underflow():
+    # reaction 2's limits leave the normal range together between 1e-12 and
+    # 1e-11 K; their quotient is finite there as elsewhere
+    import oracle
+    shape, n = (4, 16, 16), 1024
+    T = np.geomspace(3e-13, 1e-9, n)
+    U = np.zeros((binding.NFIELDS, n))
+    U[0], U[9] = 1.0, 0.3
+    U[5] = T * (1.0 - 0.15) / (binding.DEFAULT_UNITS[1] * (5.0 / 3.0 - 1.0))
+    U[4] = U[5]
+    U = U.reshape((binding.NFIELDS,) + shape)
+    P = oracle.make_params(shape, chemistry=False, cooling=True)
+    V = U.copy()
+    oracle.cooling(P, V, 1e-6)
+    box = binding.Box(shape, chemistry=False, cooling=True)
+    box.set_state(U)
+    box.debug_stage(binding.STAGE_TAIL, 1e-6)
+    e, want = box.get_state()[5], V[5]
+    there = np.isfinite(want)
+    assert there.sum() > n // 2
+    assert (np.abs(e - want)[there] <= 1e-12 * np.abs(want)[there]).all()
