@@ -636,7 +636,10 @@ __device__ __forceinline__ double cell_speed(double gamma, double rho, double mx
                                              double bx, double by, double bz)
 {
     const double rs = rsqrt_nr(rho);   // 1 / sqrt(rho)
-    const double v = root_nr(mx * mx + my * my + mz * mz) * (rs * rs);
+    // the velocities are squared, not the momenta, whose squares leave the range
+    // in units of very large or very small density
+    const double ir = rs * rs, vx = mx * ir, vy = my * ir, vz = mz * ir;
+    const double v = root_nr(vx * vx + vy * vy + vz * vz);
     const double c = root_nr(gamma * ((gamma - 1.0) * e)) * rs;
     const double ca = fabs(bx) * rs;
     const double b = root_nr(bx * bx + by * by + bz * bz) * rs;
