@@ -1147,16 +1147,17 @@ int load_f64(mhd_box* b, const double* host, bool prim, bool wait = true)
     return MHD_OK;
 }
 
-// whether the runtime holds this host memory pinned (it then copies to it at
-// the rate of the link)
-bool pinned(const void* host)
+// whether the runtime knows this memory: pinned host memory, to which it copies
+// at the rate of the link, and managed or device memory, which host threads may
+// not be able to write
+bool runtime_memory(const void* host)
 {
     hipPointerAttribute_t at;
     if (hipPointerGetAttributes(&at, host) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return at.type == hipMemoryTypeHost;
+    return at.type != hipMemoryTypeUnregistered;
 }
 
 // states below this many FP64 bytes leave in one copy of the runtime's (32^3,
@@ -1169,7 +1170,7 @@ int get_f64(mhd_box* b, HostRing& ring, double* host)
 {
     const size_t N = (size_t)b->g.n;
     const Fields<T> u = view<T>(b, b->cur[GH], b->cur[GM], b->cur[GB]);
-    if (NF * N * sizeof(double) < RING_MIN || pinned(host) || !ring_ready(ring, NF * N * sizeof(T))) {
+    if (NF * N * sizeof(double) < RING_MIN || runtime_memory(host) || !ring_ready(ring, NF * N * sizeof(T))) {
         typename BToF64<T>::Args ta;
         ta.g = b->g;
         ta.U = cview(u);
