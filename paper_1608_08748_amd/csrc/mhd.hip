@@ -973,8 +973,17 @@ void host_copy(void* dst, const void* src, size_t bytes)
                  part);
 }
 
-bool ring_ready(HostRing& r, size_t bytes)
+// Makes the ring ready for a state of this many bytes on the stream.  False,
+// for the runtime's own copy, without the memory or the events for it; on a
+// stream that is being captured, where copies are only recorded (the runtime's
+// refuses); and on a stream of another device than the events'.
+bool ring_ready(HostRing& r, size_t bytes, hipStream_t s)
 {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return false;
+    }
     const size_t want = std::min(RING_SLOT_MAX, align256((bytes + RING_SLOTS - 1) / RING_SLOTS));
     if (r.mem && r.slot < want) {   // a server's ring, sized for a smaller box
         (void)hipHostFree(r.mem);
@@ -994,6 +1003,10 @@ bool ring_ready(HostRing& r, size_t bytes)
             return false;
         }
         r.nev++;
+    }
+    if (hipEventRecord(r.ev[0], s) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
     }
     return true;
 }
@@ -1170,7 +1183,7 @@ int get_f64(mhd_box* b, HostRing& ring, double* host)
 {
     const size_t N = (size_t)b->g.n;
     const Fields<T> u = view<T>(b, b->cur[GH], b->cur[GM], b->cur[GB]);
-    if (NF * N * sizeof(double) < RING_MIN || runtime_memory(host) || !ring_ready(ring, NF * N * sizeof(T))) {
+    if (NF * N * sizeof(double) < RING_MIN || runtime_memory(host) || !ring_ready(ring, NF * N * sizeof(T), b->s)) {
         typename BToF64<T>::Args ta;
         ta.g = b->g;
         ta.U = cview(u);

@@ -9,6 +9,8 @@ typedef struct { unsigned x, y, z; } dim3_t;
 
 int stub_fail_new;        /* let the n-th array allocation of stub_new_bytes from now on fail (0: none) */
 size_t stub_new_bytes;
+int stub_capturing;       /* the stream is being captured: work is recorded, not done, and nothing can be waited for */
+int stub_other_device;    /* the events are of another device than the stream */
 
 /* operator new[](size_t, nothrow) */
 void *_ZnamRKSt9nothrow_t(size_t n, const void *tag)
@@ -37,15 +39,16 @@ int hipGetDevice(int *d) { *d = 0; return 0; }
 int hipDeviceGetAttribute(int *v, int a, int d) { (void)a; (void)d; *v = 256; return 0; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *v) { *v = 1; return 0; }
 int hipGetLastError(void) { return 0; }
-int hipStreamSynchronize(void *s) { (void)s; return 0; }
+int hipStreamSynchronize(void *s) { (void)s; return stub_capturing ? 900 : 0; }
+int hipStreamIsCapturing(void *s, int *st) { (void)s; *st = stub_capturing; return 0; }
 int hipEventCreate(void **e) { *e = malloc(1); return 0; }
 int hipEventCreateWithFlags(void **e, unsigned f) { (void)f; *e = malloc(1); return 0; }
 int hipEventDestroy(void *e) { free(e); return 0; }
-int hipEventRecord(void *e, void *s) { (void)e; (void)s; return 0; }
-int hipEventSynchronize(void *e) { (void)e; return 0; }
+int hipEventRecord(void *e, void *s) { (void)e; (void)s; return stub_other_device ? 400 : 0; }
+int hipEventSynchronize(void *e) { (void)e; return stub_capturing ? 907 : 0; }
 int hipEventElapsedTime(float *ms) { *ms = 0; return 0; }
 int hipHostMalloc(void **p, size_t n, unsigned f) { (void)f; *p = malloc(n); return 0; }
 int hipHostFree(void *p) { free(p); return 0; }
-int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *st) { (void)k; (void)st; memcpy(d, s, n); return 0; }
+int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *st) { (void)k; (void)st; if (!stub_capturing) memcpy(d, s, n); return 0; }
 int hipGetSymbolAddress(void **p) { *p = 0; return 1; }
 int hipPointerGetAttributes(void *a, const void *p) { (void)p; memset(a, 0, 32); return 0; }
