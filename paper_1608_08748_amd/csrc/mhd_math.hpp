@@ -180,7 +180,8 @@ __device__ __forceinline__ double limited_slope(double qm, double q0, double qp)
 }
 // FP32: the median of zero and two numbers is the smaller one of the same sign,
 // or zero, so two median instructions give the same value in 7 instructions
-// instead of 11 (also where the product of the two differences underflows)
+// instead of 11.  (Where the product above would underflow, differences below
+// 1e-22, this is the slope and not zero.)
 __device__ __forceinline__ float limited_slope(float qm, float q0, float qp)
 {
     const float lim = 2.0f * __builtin_amdgcn_fmed3f(0.0f, qp - q0, q0 - qm);
@@ -199,6 +200,16 @@ template <typename T> struct EtaMargin;
 template <> struct EtaMargin<double> { static constexpr double lo = 0.05 * (1.0 - 1e-9), hi = 0.1 * (1.0 + 1e-9); };
 template <> struct EtaMargin<float> { static constexpr float lo = 0.05f * (1.0f - 1e-5f), hi = 0.1f * (1.0f + 1e-5f); };
 
+// t where d is positive, -t where it is negative
+__device__ __forceinline__ float along(float t, float d)
+{
+    return __uint_as_float(__float_as_uint(t) ^ (__float_as_uint(d) & 0x80000000u));
+}
+__device__ __forceinline__ double along(double t, double d)
+{
+    return __hiloint2double(__double2hiint(t) ^ (__double2hiint(d) & (int)0x80000000u), __double2loint(t));
+}
+
 // Steps 2-5 for cell j with line values qmm..qpp, Step-1 edge values qL, qR
 // and limited slope dm of the cell
 template <typename T>
@@ -215,18 +226,18 @@ __device__ __forceinline__ Par<T> parabola_finish(T qmm, T qm, T q0, T qp, T qpp
     // Step 4: discontinuity detector on second differences (h^2 cancels):
     // eta = t / d with the weight w = clamp(20 (eta - 0.05), 0, 1), zero for
     // eta at most 0.05 or second differences of one sign.  Those two tests
-    // alone, as products with a relative margin far above rounding, leave
-    // only the cells around jumps to the rest, so most waves skip it (18 of
-    // 84 instructions; a step of 256^3 6-7% shorter in FP64 and FP32.  With
-    // the first test alone the extrema come in too: 2% more at 64^3 where
-    // nearly every wave then holds one; with every test here, 1% less at
-    // 256^3).  Where the product of two differences underflows, Step 2 is
-    // flat already.
+    // alone, without the quotient and with a relative margin far above
+    // rounding, leave only the cells around jumps to the rest, so most waves
+    // skip it (18 of 84 instructions; a step of 256^3 6-7% shorter in FP64 and
+    // FP32.  With the first test alone the extrema come in too: 2% more at 64^3
+    // where nearly every wave then holds one; with every test here, 1% less at
+    // 256^3).  The first compares magnitudes, in range wherever t and d are:
+    // t d against d^2, level in time, lost the jumps whose square overflows.
     const T Dm = q0 - T(2) * qm + qmm;
     const T Dp = qpp - T(2) * qp + q0;
     const T t = -(Dp - Dm);
     const T d = T(6) * (qp - qm);
-    if ((t * d > EtaMargin<T>::lo * (d * d)) & !(Dp * Dm > T(0))) {
+    if ((along(t, d) > EtaMargin<T>::lo * fabs(d)) & !(Dp * Dm > T(0))) {
         // the smallest of |q_{i+1}|, |q_{i-1}| and their sum is one of the two
         const T mn = fmin(fabs(qp), fabs(qm));
         const bool zero_eta = fabs(qp - qm) - T(0.01) * mn <= T(0);
