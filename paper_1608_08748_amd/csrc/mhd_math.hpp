@@ -444,11 +444,12 @@ struct ChemArgs {
     double e_rate;  // t_unit / (n_unit k_B T_unit): erg cm^-3 s^-1 to code energy density per code time
 };
 
-// a / b from r = rcp_nr(b)
+// a / b from r = rcp_nr(b); the last instruction gives the quotients with zeros
+// and infinities, which have no residual
 __device__ __forceinline__ double quot(double a, double b, double r)
 {
     const double q = a * r;
-    return fma(fma(-b, q, a), r, q);
+    return __builtin_amdgcn_div_fixup(fma(fma(-b, q, a), r, q), b, a);
 }
 __device__ __forceinline__ double quot(double a, double b) { return quot(a, b, rcp_nr(b)); }
 
