@@ -59,12 +59,13 @@ extern "C" {
 enum {
     MHD_OK = 0,
     MHD_EINVAL = -1,     /* bad argument (dims, NULL, dt not finite or <= 0, ...) */
-    MHD_ENOMEM = -2,     /* workspace missing or smaller than mhd_workspace_bytes */
+    MHD_ENOMEM = -2,     /* workspace missing or smaller than mhd_workspace_bytes, */
+                         /* or no host memory                                     */
     MHD_EDEVICE = -3,    /* a HIP runtime call failed                             */
     MHD_ECFL = -4,       /* a step used dt above the CFL bound of its start state */
     MHD_ENONPHYS = -5,   /* non-finite or non-positive rho or e after a step       */
-    MHD_ETOOLARGE = -6   /* box beyond the static scratch of an allocation-free    */
-                         /* entry point (MHD_NOALLOC_MAX_CELLS)                    */
+    MHD_ETOOLARGE = -6   /* box beyond what the allocation-free entry point takes  */
+                         /* (MHD_NOALLOC_MAX_CELLS)                                */
 };
 
 enum { MHD_FP64 = 0, MHD_FP32_MIXED = 1 };

@@ -494,14 +494,14 @@ int best_segment(int nd, double units, int slots, int occ, double more, double f
 
 // tiles of the face-field update: 64 x cells (a wave) by nt / 64 rows for
 // blocks of nt threads, narrower for thin boxes
-ZTile ztile_of(const Geo& g, int nt, int txmax)
+ZTile ztile_of(const Geo& g, int nt, int txmax, int seg)
 {
     ZTile z;
     z.tx = g.nx < txmax ? g.nx : txmax;
     z.ty = nt / z.tx;
     z.ntx = (g.nx + z.tx - 1) / z.tx;
     z.nty = (g.ny + z.ty - 1) / z.ty;
-    z.seg = g.nz < ZMARCH_SEG ? g.nz : ZMARCH_SEG;
+    z.seg = seg;
     return z;
 }
 
@@ -640,8 +640,7 @@ void emit_nonadv_substage_t(mhd_box* b, Emit& e, Slots sin, Slots sS, Slots sout
     ua.a = a;
     ua.rk = rk;
     ua.dbg = dbg;
-    ua.zt = ztile_of(g, UPD_NT, UPD_TX);
-    ua.zt.seg = b->seg_b;
+    ua.zt = ztile_of(g, UPD_NT, UPD_TX, b->seg_b);
     e.template launch<BFieldUpdate<T, O>>(MHD_K_NONADV_UPDATE, ztile_blocks(g, ua.zt), 0, ua);
 }
 
@@ -1840,11 +1839,11 @@ const char* mhd_strerror(int status)
     switch (status) {
     case MHD_OK: return "ok";
     case MHD_EINVAL: return "invalid argument";
-    case MHD_ENOMEM: return "workspace missing or too small";
+    case MHD_ENOMEM: return "workspace missing or too small, or no host memory";
     case MHD_EDEVICE: return "HIP runtime error";
     case MHD_ECFL: return "time step above the CFL bound";
     case MHD_ENONPHYS: return "non-finite or non-positive density or internal energy";
-    case MHD_ETOOLARGE: return "box larger than the static scratch of the allocation-free entry point";
+    case MHD_ETOOLARGE: return "box larger than the allocation-free entry point (on static scratch) takes";
     default: return "unknown status";
     }
 }

@@ -39,18 +39,8 @@ struct RK { double a, b; };
 
 // ---------------------------------------------------------------- launch wrappers
 
-// Workgroups are dealt to the 8 XCDs round robin (workgroup b runs on XCD
-// b % 8) and each XCD has its own L2.  This bijection gives every XCD one
-// contiguous range of logical blocks, so stencil neighbours in the next row
-// or plane are read through the same L2.
-__device__ __forceinline__ int xcd_block(int b, int nb)
-{
-    constexpr int X = 8;
-    int q = nb / X, r = nb % X, x = b % X, i = b / X;
-    return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
-}
-
-// XCD bands: a launch whose logical blocks are L = (s * nb + y) * ni + i
+// XCD bands: workgroups are dealt to the 8 XCDs round robin (workgroup b runs on
+// XCD b % 8) and each XCD has its own L2.  A launch whose logical blocks are L = (s * nb + y) * ni + i
 // (i < ni fastest, then y < nb, then s) deals y in eight contiguous bands, one
 // per XCD, over every s: at any moment the eight XCDs work on the same s at
 // bands nb / 8 apart, and the neighbours at y +- 1 and s + 1 of a block mostly
@@ -67,14 +57,6 @@ __device__ __forceinline__ int xcd_band(int b, int ni, int nb, int ns)
     const int x = b % 8, q = b / 8;
     const int s = q / per, l = q - s * per;
     return (s * nb + x * (nb / 8) + l / ni) * ni + l % ni;
-}
-
-// kernels whose stencil spans neighbouring rows of other blocks opt in with
-// `static constexpr bool XCD = true`
-template <class Body>
-__device__ __forceinline__ int logical_block()
-{
-    return Body::XCD ? xcd_block((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
 }
 
 // Cell column (i, j) and z segment of a thread of a z-marching kernel: blocks
@@ -158,14 +140,14 @@ template <class Body> struct MinWaves<Body, std::void_t<decltype(Body::MINW)>> {
 template <class Body>
 __global__ __launch_bounds__(Body::NT) __attribute__((amdgpu_waves_per_eu(MinWaves<Body>::v))) void k_one(typename Body::Args a)
 {
-    Body::run(a, logical_block<Body>(), (int)threadIdx.x);
+    Body::run(a, (int)blockIdx.x, (int)threadIdx.x);
 }
 
 template <class Body>
 __global__ __launch_bounds__(Body::NT) __attribute__((amdgpu_waves_per_eu(MinWaves<Body>::v))) void k_many(const typename Body::Args* __restrict__ tab,
                                                    const int* __restrict__ bstart, int nbox)
 {
-    int blk = logical_block<Body>();
+    const int blk = (int)blockIdx.x;
     int lo = 0, hi = nbox - 1;
     while (lo < hi) {
         int mid = (lo + hi + 1) >> 1;
@@ -355,7 +337,6 @@ constexpr int XROW_SLOTS = 18;
 template <typename T, int MAXT, bool ION, class O>
 struct BFaceXRows {
     static constexpr int NT = MAXT;
-    static constexpr bool XCD = false;
     // FP32 rows keep one workgroup per tile in the persistent multi-box form:
     // the tile loop costs three registers (83 instead of 80), five waves per
     // SIMD instead of six, and these small tiles run 8% slower (held to six
@@ -590,7 +571,6 @@ struct BFaceXRows {
 template <typename T, bool ION, class O>
 struct BFaceMarch {
     static constexpr int NT = NTH;
-    static constexpr bool XCD = false;
     // two waves per SIMD (FP64 needs 254-258 registers unbounded)
     static constexpr int MINW = sizeof(T) == 8 ? 2 : 1;
     using Args = FaceArgs<T>;
@@ -787,7 +767,6 @@ constexpr int UPD_TX = 64;
 template <typename T, class O>
 struct BFieldUpdate {
     static constexpr int NT = UPD_NT;
-    static constexpr bool XCD = false;
     static constexpr int MINW = 4;
     using Args = FieldUpdateArgs<T>;
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
@@ -1015,7 +994,6 @@ struct FftArgs {
 template <typename T, int INV>
 struct BFftX {
     static constexpr int NT = NTH;
-    static constexpr bool XCD = false;
     using Args = FftArgs<T>;
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
     {
@@ -1069,7 +1047,6 @@ struct BFftX {
 template <typename T, int D, int MODE>
 struct BFftYZ {
     static constexpr int NT = NTH;
-    static constexpr bool XCD = false;
     using Args = FftArgs<T>;
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
     {
@@ -1187,20 +1164,17 @@ __device__ __forceinline__ double tail_speed(const StepArgs& a, double rho, doub
 
 // ADV faces along y, marched: each thread walks one y line over a segment of
 // `seg` cells with a sliding 5-cell window of the NQ fields, so each cell's
-// limited slope, lower interface value and parabola are formed once (the
-// per-face kernel forms three slopes, two interface values and a parabola per
-// face); the previous cell's right side and sqrt(rho) are carried.  The face
-// takes the upwind average: the left cell's right part for vf >= 0, the right
-// cell's left part otherwise (the same arithmetic as the x faces).  What is
-// stored is each cell's flux difference F(upper face) - F(lower face), the
-// value the update takes, so the segment forms one face more than it has
-// cells (the upper face of its last cell, also formed by the next segment
-// from the same window) and the update reads one value per field instead of
-// two.
+// limited slope, lower interface value and parabola are formed once; the
+// previous cell's right side and sqrt(rho) are carried.  The face takes the
+// upwind average: the left cell's right part for vf >= 0, the right cell's left
+// part otherwise (the same arithmetic as the x faces).  What is stored is each
+// cell's flux difference F(upper face) - F(lower face), the value the update
+// takes, so the segment forms one face more than it has cells (the upper face
+// of its last cell, also formed by the next segment from the same window) and
+// the update reads one value per field instead of two.
 template <typename T, int NQ, class O>
 struct BAdvFaceMarchY {
     static constexpr int NT = NTH;
-    static constexpr bool XCD = false;
     // two waves per SIMD (FP64 needs 220-230 registers; unbounded, the
     // scheduler may take a few more and halve that)
     static constexpr int MINW = sizeof(T) == 8 ? 2 : 1;
@@ -1337,9 +1311,9 @@ struct BAdvFaceMarchY {
 // cell's parabola from its 5-cell window at fixed offsets); the fluxes are
 // exchanged through LDS for the x difference, so the x fluxes never pass
 // through memory; the y difference comes from memory (stored by the y march).
-// The fields are split over two launches so that a thread holds a small window
-// and more waves fit on a SIMD; both read rho and the momenta of the faces for
-// the face velocities.  At 256^3 FP64 the two groups take 0.97 ms (1.13 before
+// The fields are split in two groups of blocks (BAdvXZPair) so that a thread
+// holds a small window and more waves fit on a SIMD; both read rho and the
+// momenta of the faces for the face velocities.  At 256^3 FP64 the two groups take 0.97 ms (1.13 before
 // the parabola's early tests and the shared launch), FP32 0.47 (0.60): 31 values
 // per cell at 4.3 TB/s, the VALU 73% busy.  Three block barriers per plane
 // (values, slopes, fluxes; two were level); the LDS is double-buffered by plane parity, so a buffer is
@@ -1366,7 +1340,6 @@ struct AdvXZArgs {
 template <typename T, int Q0, int NQ, int MAXT, class O>
 struct BAdvXZUpdate {
     static constexpr int NT = MAXT;
-    static constexpr bool XCD = false;
     // rho and m of the cell are window fields 0-3 of the first group;
     // the energy group stages rho and mx of the cell as two more values
     static constexpr bool own_v = Q0 == 0 && NQ >= 4;
@@ -1631,7 +1604,6 @@ struct BAdvXZPair {
     using G1 = BAdvXZUpdate<T, 0, 4, MAXT, O>;
     using G2 = BAdvXZUpdate<T, 4, NQ2, MAXT, O>;
     static constexpr int NT = MAXT;
-    static constexpr bool XCD = false;
     static constexpr int MINW = G1::MINW;
     using Args = AdvXZArgs<T>;
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
@@ -1653,7 +1625,6 @@ struct BAdvXZPair {
 template <typename T, class O>
 struct BTail {
     static constexpr int NT = NTH;
-    static constexpr bool XCD = false;
     // in a resident loop the compiler keeps the chemistry's FP64 constants in
     // registers across tiles (174 instead of 98: half the waves per SIMD)
     static constexpr bool PERSIST = false;
@@ -1702,7 +1673,6 @@ struct BTail {
 // result equals the minimum over cells of cfl h / speed)
 struct BReduceDt {
     static constexpr int NT = 1024;
-    static constexpr bool XCD = false;
     struct Args {
         const double* part;
         int nparts;
@@ -1740,7 +1710,6 @@ struct BReduceDt {
 template <typename T>
 struct BTotalsPartial {
     static constexpr int NT = NTH;
-    static constexpr bool XCD = false;
     static constexpr int ACC = 8;
     struct Args {
         int n, per, chunks;
@@ -1775,7 +1744,6 @@ struct BTotalsPartial {
 
 struct BTotalsFinal {
     static constexpr int NT = 64 * NF;
-    static constexpr bool XCD = false;
     struct Args {
         const double* part;
         int chunks;
@@ -1799,7 +1767,6 @@ struct BTotalsFinal {
 template <typename T>
 struct BInit {
     static constexpr int NT = NTH;
-    static constexpr bool XCD = false;
     struct Args {
         Geo g;
         const double* Wp;
@@ -1842,7 +1809,6 @@ struct BInit {
 template <typename T>
 struct BFromF64 {
     static constexpr int NT = NTH;
-    static constexpr bool XCD = false;
     struct Args {
         Geo g;
         const double* src;
@@ -1861,7 +1827,6 @@ struct BFromF64 {
 template <typename T>
 struct BToF64 {
     static constexpr int NT = NTH;
-    static constexpr bool XCD = false;
     struct Args {
         Geo g;
         CFields<T> U;
@@ -1879,7 +1844,6 @@ struct BToF64 {
 
 struct BClearFlags {
     static constexpr int NT = 64;
-    static constexpr bool XCD = false;
     struct Args {
         uint32_t* flags;
     };
