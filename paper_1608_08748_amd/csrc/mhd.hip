@@ -676,7 +676,7 @@ void emit_adv_xz(Emit& e, const AdvXZArgs<T>& xa, bool ion)
 {
     using O = typename Emit::Access;
     auto shm = [](int nv, int nq) { return (size_t)2 * (nv + 2 * nq) * NT * sizeof(T); };
-    const int both = (xa.tiles + 7) / 8 * 16;
+    const int both = 2 * xa.tiles;
     if (!ion) {
         e.template launch<BAdvXZPair<T, 3, NT, O>>(MHD_K_ADV_UPDATE, both, shm(4, 4), xa, 2);
     } else if constexpr (sizeof(T) == 4) {

@@ -1596,7 +1596,11 @@ struct BAdvXZUpdate {
 // Both field groups in one launch, eight tiles of the first group and the same
 // eight of the second in turn, so that a tile's two blocks run on one XCD (block
 // b on XCD b % 8) at about the same time and share their rho and momenta in its
-// L2; a small box pays the latency of one march instead of two.  (FP64 with the
+// L2; a small box pays the latency of one march instead of two.  Of the last
+// tiles, fewer than eight, the second group's follow the first's without a gap:
+// with idle blocks up to the next eight every box of a served batch started on
+// XCD 0, and boxes of one tile left the other seven idle (256 boxes of 16^3 FP64
+// 512 us a launch, two launches 120 us; 64 of 32^3 291 and 224).  (FP64 with the
 // H+ field keeps two launches: the second group's registers leave two waves per
 // SIMD, the first group alone three.)
 template <typename T, int NQ2, int MAXT, class O>
@@ -1608,10 +1612,12 @@ struct BAdvXZPair {
     using Args = AdvXZArgs<T>;
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
     {
-        const int tile = (blk >> 4) * 8 + (blk & 7);
-        if (tile >= A.tiles) return;   // the whole block: before any barrier
-        if (blk & 8) G2::run(A, tile, tid);
-        else G1::run(A, tile, tid);
+        const int last = A.tiles & ~7;   // tiles in eights
+        const int of = blk < 2 * last ? 8 : A.tiles - last;
+        const int l = blk < 2 * last ? blk & 15 : blk - 2 * last;
+        const int t0 = blk < 2 * last ? (blk >> 4) * 8 : last;
+        if (l < of) G1::run(A, t0 + l, tid);
+        else G2::run(A, t0 + l - of, tid);
     }
 };
 
