@@ -132,6 +132,13 @@ __device__ __forceinline__ RowCell row_cell(const Geo& g, const RowTile& t, int 
     return c;
 }
 
+// Dynamic LDS starts behind a kernel's static LDS.  Both are in units of 16 bytes:
+// behind a claim slot of 4 bytes every FP64 access of a resident launch was
+// misaligned and took three times as long (64 boxes of 32^3 FP64: x rows 325 ->
+// 126 us a launch, ADV update 653 -> 168 with its idle blocks gone too).
+constexpr int LDS_ALIGN = 16;
+using DYN_LDS = __attribute__((aligned(LDS_ALIGN))) unsigned char;
+
 // occupancy floor: a body may ask for at least MINW waves per SIMD (the
 // compiler then caps its registers); default 1
 template <class Body, class = void> struct MinWaves { static constexpr int v = 1; };
@@ -179,7 +186,8 @@ __global__ __launch_bounds__(Body::NT) __attribute__((amdgpu_waves_per_eu(MinWav
                                                    const int* __restrict__ bstart, int nbox, int total, int chunk,
                                                    int* next)
 {
-    __shared__ int taken;
+    __shared__ __attribute__((aligned(LDS_ALIGN))) int slot[LDS_ALIGN / sizeof(int)];
+    int& taken = slot[0];
     int box = 0;
     for (;;) {
         if (threadIdx.x == 0) taken = atomicAdd(next, chunk);
@@ -351,7 +359,7 @@ struct BFaceXRows {
     }
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
     {
-        extern __shared__ unsigned char smem_raw[];
+        extern __shared__ DYN_LDS smem_raw[];
         T* sm = reinterpret_cast<T*>(smem_raw);
         const Geo& g = A.g;
         const size_t N = (size_t)g.n;
@@ -997,7 +1005,7 @@ struct BFftX {
     using Args = FftArgs<T>;
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
     {
-        extern __shared__ unsigned char smem_raw[];
+        extern __shared__ DYN_LDS smem_raw[];
         const int n = A.g.nx, logn = A.logn[0];
         Cx<T>* a = reinterpret_cast<Cx<T>*>(smem_raw);
         const int lines = A.g.ny * A.g.nz;
@@ -1050,7 +1058,7 @@ struct BFftYZ {
     using Args = FftArgs<T>;
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
     {
-        extern __shared__ unsigned char smem_raw[];
+        extern __shared__ DYN_LDS smem_raw[];
         const Geo& g = A.g;
         const int n = D == 1 ? g.ny : g.nz, logn = A.logn[D];
         const int logt = A.logt, tx = 1 << logt, ls = n + 1;
@@ -1350,7 +1358,7 @@ struct BAdvXZUpdate {
     using Args = AdvXZArgs<T>;
     static __device__ __forceinline__ void run(const Args& A, int blk, int tid)
     {
-        extern __shared__ unsigned char smem_raw[];
+        extern __shared__ DYN_LDS smem_raw[];
         T* sm = reinterpret_cast<T*>(smem_raw);
         const Geo& g = A.g;
         const int rg = blk % A.nrg, sgi = blk / A.nrg;
