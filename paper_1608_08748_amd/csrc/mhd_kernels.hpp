@@ -1632,9 +1632,9 @@ struct BAdvXZPair {
 // ---------------------------------------------------------------- tail and reductions
 
 // Tail of the step (after ADV) as a pass of its own: tail_cell on every cell,
-// validity flag, per-block CFL speed maximum.  12 values per cell: 281 us at
-// 256^3 FP64, 5.7 TB/s (381 us when its divisions and exponentials bound it),
-// FP32 238 us (377).
+// validity flag, per-block CFL speed maximum.  12 values per cell: 291 us at
+// 256^3 FP64, 5.7 TB/s of traffic (381 us when its divisions and exponentials
+// bound it), FP32 241 us (377).
 // mode: 1 = full tail, 0 = speed only (state unchanged).
 template <typename T, class O>
 struct BTail {
@@ -1718,9 +1718,9 @@ struct BReduceDt {
 // cells of one field, each thread eight running sums over every 256th cell, so
 // that eight loads are in flight per thread and the sums carry few terms;
 // then one wave per field sums the chunks.  Bound by the read of the state: at
-// 256^3 FP64 (1.48 GB) the pass takes 238 us, 6.2 TB/s.  (One block per 256
-// cells of all fields left 65536 x 11 partial sums to a single last block:
-// 978 us in all.)
+// 256^3 FP64 (1.48 GB) both launches take 238 us, 6.2 TB/s, one after another; a
+// single one behind steps 260.  (One block per 256 cells of all fields left
+// 65536 x 11 partial sums to a single last block: 978 us in all.)
 template <typename T>
 struct BTotalsPartial {
     static constexpr int NT = NTH;

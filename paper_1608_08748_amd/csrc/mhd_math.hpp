@@ -433,7 +433,7 @@ __device__ __forceinline__ void face_solve(T rl, T pl, T b1l, T b2l, T rr, T pr,
 // rounding at exponents near 30 is the error, the limits of reaction 2 were 2.5
 // times as far off (rms 9e-15 against 3.6e-15), and a rate applied to num / den
 // instead of the quotient left the H2 update a fifth further off.  That costs
-// 7 of 57 us of the tail at 96^3 with everything on, 11 of 238 us at 256^3 FP32.
+// 7 of 56 us of the tail at 96^3 with everything on, 16 of 241 us at 256^3 FP32.
 
 struct ChemArgs {
     int on;     // chemistry stage
